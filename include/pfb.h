@@ -120,12 +120,18 @@ typedef struct pfb_plan pfb_plan;
 
 /* Description of what a plan will run, for reports and tests. */
 typedef struct {
-    int32_t path;          /* 0 fused FIR+FFT, 1 split FIR then FFT, 2 FIR only */
+    int32_t path;          /* 0 fused FIR+FFT over a register window, 1 split:
+                              FIR, then FFT of its results, by two launches
+                              through the workspace or, for a whole forward
+                              call of the sizes it covers, by one launch that
+                              keeps the results of a block of spectra on the
+                              chip (same bits); 2 FIR only                  */
     int32_t fir_rows;      /* filtered spectra per FIR tile (S_B)              */
     int32_t fir_cpt;       /* channels per thread in the FIR kernel            */
     int32_t padded_taps;   /* taps rounded up to the kernel's template size    */
     int64_t workspace_bytes;
-    int64_t chunk_rows;    /* spectra per FIR/FFT chunk on the split path      */
+    int64_t chunk_rows;    /* spectra per FIR/FFT chunk on the split path (per
+                              block where one launch runs both)            */
     int32_t backward_fused;/* pfb_backward runs: 0 the split adjoint (inverse
                               FFT, reversed-tap FIR, tap-gradient pass),
                               1 the fused adjoint kernel, 2 its

@@ -99,6 +99,7 @@ struct pfb_plan {
     bool fused_ws = false;       // wave-specialised fused kernel
     // split path chunking
     int64_t chunk_rows = 0;
+    bool blocked = false;        // FIR and FFT in one launch, block by block (block_launch.h)
     float2 *twiddle = nullptr;   // FFT twiddle table for C
     bool mixed = false;          // C not a power of two: mixed-radix transform
     bool long_fir = false;       // T beyond the register window
@@ -296,6 +297,14 @@ static int view_rows_cap(int64_t row_bytes, int rb, int extra)
     return (int)(cap < rb ? rb : (cap > INT32_MAX ? INT32_MAX / rb * rb : cap));
 }
 
+static int64_t row_bytes_in(const pfb_desc &d) { return (int64_t)d.channels * bytes_per_sample(d.dtype); }
+
+// The blocked kernel addresses a block's raw rows through one bounded view.
+static bool block_views_fit(int64_t row_bytes, int rows, int tp)
+{
+    return row_bytes * (rows + tp) <= 0x7fffffff;
+}
+
 // Rows per fused tile: whole rounds over the workgroups that fit at once
 // (`slots`), at least 256 rows so that the T-1 halo rows a tile re-reads stay
 // a small fraction of its input (measured: 64-row tiles fetched 1.24x the
@@ -399,7 +408,17 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
         // than they gain); above 4 GiB, or with a tuned chunk size, the
         // rows are processed in chunks.
         const int64_t row_bytes = (int64_t)d->channels * 8;
-        if (p->path == PATH_SPLIT) {
+        if (p->path == PATH_SPLIT && !(d->flags & (PFB_NO_FUSE | PFB_PLAIN | PFB_CONVERT_PER_USE)) && p->log2c >= 0 &&
+            !p->long_fir && block_supported(d->dtype, p->tp, p->log2c, false) && block_views_fit(row_bytes_in(*d), block_rows(p->log2c, false), p->tp)) {
+            // a tuned chunk size asks for the two launches
+            p->blocked = tuned && te.block >= 0 ? te.block != 0
+                         : tuned && te.chunk_mib > 0
+                             ? false
+                             : block_pays(d->dtype, p->tp, p->log2c, false, d->batch, d->spectra);
+        }
+        if (p->blocked) {
+            p->chunk_rows = block_rows(p->log2c, false);
+        } else if (p->path == PATH_SPLIT) {
             if (d->flags & PFB_PLAIN) {
                 p->chunk_rows = d->spectra;
             } else {
@@ -534,6 +553,24 @@ static hipError_t run_fir(const pfb_plan *p, const void *x, const float *h, floa
     return launch_fir(a, d.dtype, p->tp, p->fir_cpt, false, st, (d.flags & PFB_CONVERT_PER_USE) != 0);
 }
 
+// FIR and FFT of a whole forward call in one launch (streams, or the
+// polarisation-interleaved sub-bands of a plan that has them).
+static hipError_t run_block(const pfb_plan *p, const void *x, const float *h, float2 *Y, hipStream_t st)
+{
+    const bool pol = p->vegas_cv > 0;
+    BlockArgs a{};
+    a.x = x;
+    a.h = h;
+    a.Y = Y;
+    a.tw = p->twiddle;
+    a.T = p->d.taps;
+    a.num_cus = p->num_cus;
+    a.S = p->d.spectra;
+    a.units = pol ? p->vegas_nsub : p->d.batch;
+    a.nsub = p->vegas_nsub;
+    return launch_block(a, p->d.dtype, p->tp, pol ? p->vegas_log2cv : p->log2c, pol, st);
+}
+
 static hipError_t run_fft(const pfb_plan *p, const float2 *in, float2 *out, int64_t nrows, int64_t rows_per_group,
                           int64_t in_gstride, int64_t out_gstride, bool inv, hipStream_t st)
 {
@@ -609,6 +646,10 @@ extern "C" pfb_status pfb_execute(pfb_plan *p, const void *x, const float *taps,
         if (e == hipSuccess)
             e = run_fft(p, yo, Yo, (int64_t)d.batch * S, S, S * C, S * C, false, st);
         return e == hipSuccess ? PFB_OK : hip_fail(e, "split FIR/FFT launch");
+    }
+    if (p->blocked) {
+        e = run_block(p, x, taps, Yo, st);
+        return e == hipSuccess ? PFB_OK : hip_fail(e, "blocked FIR+FFT launch");
     }
     // chunked split path through the plan's workspace
     for (int64_t s_a = 0; s_a < S; s_a += p->chunk_rows) {
@@ -708,12 +749,14 @@ extern "C" pfb_status pfb_plan_create_vegas(int32_t channels, int32_t subbands, 
         p->vegas_nsub = subbands;
         p->vegas_log2cv = l2;
         st = make_twiddles(l2, &p->twiddle);
+        p->blocked = !p->long_fir && block_pays(dtype, p->tp, l2, true, subbands, spectra) &&
+                     block_views_fit(row_bytes_in(d), block_rows(l2, true), p->tp);
     }
-    if (st == PFB_OK) {
+    if (st == PFB_OK && !p->blocked) {
         p->ws_y_bytes = spectra * cols * 8;
         st = dev_alloc(reinterpret_cast<void **>(&p->ws_y), p->ws_y_bytes, "filtered spectra");
     }
-    if (st == PFB_OK)
+    if (st == PFB_OK && !p->blocked)
         st = dev_alloc(reinterpret_cast<void **>(&p->h_rep), (int64_t)taps * cols * 4, "replicated taps");
     if (st != PFB_OK) {
         free_plan_memory(p);
@@ -736,6 +779,10 @@ extern "C" pfb_status pfb_execute_vegas(pfb_plan *p, const void *x, const float 
         return fail(PFB_E_INVALID, "device pointers must be 16-byte aligned");
     const pfb_desc &d = p->d;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    if (p->blocked) {
+        const hipError_t eb = run_block(p, x, taps, reinterpret_cast<float2 *>(Y), st);
+        return eb == hipSuccess ? PFB_OK : hip_fail(eb, "blocked sub-band launch");
+    }
     hipError_t e = launch_vegas_taps(taps, p->h_rep, d.taps, p->vegas_cv, p->vegas_nsub, st);
     if (e == hipSuccess)
         e = run_fir(p, x, p->h_rep, p->ws_y, 0, d.spectra, d.spectra * d.channels, st);

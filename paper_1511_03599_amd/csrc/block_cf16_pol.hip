@@ -1,0 +1,11 @@
+// Blocked FIR + FFT (block_launch.h) for cf16 input, polarisation-interleaved sub-bands.
+#include "block_launch.h"
+
+namespace pfb {
+
+hipError_t launch_block_cf16_pol(const BlockArgs &a, int tp, int log2c, hipStream_t st)
+{
+    return launch_block_pol<DT_CF16>(a, tp, log2c, st);
+}
+
+} // namespace pfb

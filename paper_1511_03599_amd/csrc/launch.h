@@ -75,6 +75,21 @@ struct FusedArgs {
     int64_t S;
 };
 
+// Blocked FIR + FFT (block_launch.h): blocks of whole filtered spectra of one
+// stream, or of one sub-band with two interleaved polarisations.
+struct BlockArgs {
+    const void *x;       // [units][S+T-1][C], or [S+T-1][nsub][C][2]
+    const float *h;      // [T][C]
+    float2 *Y;           // [units][S][C], or [S][nsub][C][2]
+    const float2 *tw;
+    int T;
+    int num_cus;
+    int64_t S;
+    int64_t units;       // streams, or sub-bands
+    int64_t nsub;        // sub-bands of a row (polarisation-interleaved layout)
+    int64_t n_blocks;    // blocks per unit (set by the launcher)
+};
+
 // Fused adjoint: one workgroup per tile of S_B gx rows of one stream.
 struct BwdArgs {
     const float2 *x;     // [B][S+T-1][C]
@@ -126,6 +141,20 @@ hipError_t launch_fused(const FusedArgs &a, int dtype, int tp, int log2c, hipStr
 hipError_t launch_fused_ci16(const FusedArgs &a, int tp, int log2c, hipStream_t st);
 hipError_t launch_fused_ci8(const FusedArgs &a, int tp, int log2c, hipStream_t st);
 hipError_t launch_fused_cf16(const FusedArgs &a, int tp, int log2c, hipStream_t st);
+// per input type and group of sizes (each in its own translation unit)
+#define PFB_BLOCK_DECL(NAME)                                                                                 \
+    hipError_t launch_block_##NAME##_small(const BlockArgs &a, int tp, int log2c, hipStream_t st);           \
+    hipError_t launch_block_##NAME##_large(const BlockArgs &a, int tp, int log2c, hipStream_t st);           \
+    hipError_t launch_block_##NAME##_pol(const BlockArgs &a, int tp, int log2c, hipStream_t st);
+PFB_BLOCK_DECL(c64)
+PFB_BLOCK_DECL(ci16)
+PFB_BLOCK_DECL(ci8)
+PFB_BLOCK_DECL(cf16)
+#undef PFB_BLOCK_DECL
+hipError_t launch_block(const BlockArgs &a, int dtype, int tp, int log2c, bool pol, hipStream_t st);
+bool block_supported(int dtype, int tp, int log2c, bool pol);
+int block_rows(int log2c, bool pol); // filtered spectra per block
+bool block_pays(int dtype, int tp, int log2c, bool pol, int64_t units, int64_t S);
 hipError_t launch_fused_ws(const FusedArgs &a, int dtype, int tp, int log2c, hipStream_t st);
 // nblk blocks of `bytes` bytes from src + b*src_stride to dst + b*dst_stride
 // (src NULL: zeros).

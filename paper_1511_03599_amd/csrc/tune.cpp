@@ -1,6 +1,6 @@
 // Tuning cache: a small text file, one entry per line,
 //   <arch> <dtype> <C> <T> <B> <S> path=<p> fir_cpt=<n> fir_sb=<n> fused_sb=<n> fused_ws=<n> chunk_mib=<n>
-//   bwd_sb=<n> bwd_ws=<n>
+//   bwd_sb=<n> bwd_ws=<n> block=<n>
 // for single plans, and
 //   <arch> batched <nbeams> <total samples> tile_kib=<n>
 // for batched plans.
@@ -95,6 +95,7 @@ bool tune_lookup(const pfb_desc &d, TuneEntry *out)
             parse_kv(tok, "chunk_mib", &e.chunk_mib);
             parse_kv(tok, "bwd_sb", &e.bwd_sb);
             parse_kv(tok, "bwd_ws", &e.bwd_ws);
+            parse_kv(tok, "block", &e.block);
         }
         if (B == d.batch && S == d.spectra) {
             best_exact = e; // the last matching line wins
@@ -303,6 +304,7 @@ extern "C" pfb_status pfb_tune(const pfb_desc *desc, const char *cache_path)
                         e.fir_cpt = cpt;
                         e.fir_sb = sb;
                         e.chunk_mib = mib;
+                        e.block = 0;
                         cands.push_back(e);
                     }
                 }
@@ -325,6 +327,15 @@ extern "C" pfb_status pfb_tune(const pfb_desc *desc, const char *cache_path)
                 }
         }
         add_split(1);
+        if (!(d.flags & (PFB_NO_FUSE | PFB_PLAIN | PFB_CONVERT_PER_USE)) && l2 >= 0 && d.taps <= PFB_MAX_TAPS_WINDOW &&
+            block_supported(d.dtype, tp, l2, false)) {
+            TuneEntry e;
+            e.path = 1;
+            e.block = 1;
+            e.fir_cpt = cpt2 ? 2 : 1; // of calls that keep the filtered spectra
+            e.fir_sb = 32;
+            cands.push_back(e);
+        }
     }
     const int reps = 7;
     double best_t = -1.0;
@@ -332,8 +343,8 @@ extern "C" pfb_status pfb_tune(const pfb_desc *desc, const char *cache_path)
     for (const TuneEntry &e : cands) {
         const double t = time_candidate(d, e, buf, s, reps);
         if (verbose)
-            std::fprintf(stderr, "pfb_tune: path=%d fir_cpt=%d fir_sb=%d fused_ws=%d fused_sb=%d chunk_mib=%d -> %.4f ms\n",
-                         e.path, e.fir_cpt, e.fir_sb, e.fused_ws, e.fused_sb, e.chunk_mib, t);
+            std::fprintf(stderr, "pfb_tune: path=%d fir_cpt=%d fir_sb=%d fused_ws=%d fused_sb=%d chunk_mib=%d block=%d -> %.4f ms\n",
+                         e.path, e.fir_cpt, e.fir_sb, e.fused_ws, e.fused_sb, e.chunk_mib, e.block, t);
         if (t > 0 && (best_t < 0 || t < best_t)) {
             best_t = t;
             best = e;
@@ -373,10 +384,10 @@ extern "C" pfb_status pfb_tune(const pfb_desc *desc, const char *cache_path)
         return pfb_internal_fail(PFB_E_INVALID, "cannot open the tuning cache for writing");
     std::fprintf(f,
                  "%s %d %d %d %d %lld path=%d fir_cpt=%d fir_sb=%d fused_sb=%d fused_ws=%d chunk_mib=%d bwd_sb=%d "
-                 "bwd_ws=%d ms=%.5f\n",
+                 "bwd_ws=%d block=%d ms=%.5f\n",
                  device_arch_name().c_str(), d.dtype, d.channels, d.taps, d.batch, (long long)d.spectra, best.path,
                  best.fir_cpt, best.fir_sb, best.fused_sb, best.fused_ws, best.chunk_mib, best.bwd_sb, best.bwd_ws,
-                 best_t);
+                 best.block, best_t);
     std::fclose(f);
     return PFB_OK;
 }

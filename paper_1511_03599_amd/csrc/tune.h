@@ -16,6 +16,7 @@ struct TuneEntry {
     int fused_sb = 0;    // fused rows per tile
     int fused_ws = -1;   // fused forward: 1 wave-specialised, 0 single-role, -1 not set
     int chunk_mib = 0;   // split-path chunk size
+    int block = -1;      // split path: 1 FIR and FFT in one launch, block by block, 0 two launches, -1 not set
     int bwd_sb = 0;      // fused adjoint rows per tile
     int bwd_ws = -1;     // fused adjoint: 1 wave-specialised, 0 single-role, -1 not set
 };
