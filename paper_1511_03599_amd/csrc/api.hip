@@ -262,30 +262,54 @@ static pfb_status dev_alloc(void **p, int64_t bytes, const char *what)
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Rows per tile for a kernel that runs one workgroup per CU at a time: the
-// smallest multiple of `rb` that is at least `min_rows` and splits the
-// B*rows work into a whole number of rounds over the CUs (so that no CU
-// runs one tile more than the others at the end).
-static int balanced_tile_rows(int64_t B, int64_t rows, int rb, int64_t min_rows, int cus)
+// Rows per tile (a multiple of rb) for B streams of `rows` rows, one
+// workgroup per tile, `slots` workgroups at once. Two things bound a launch,
+// in rows of work per slot:
+//   path   the slot with the most tiles: its tiles' rows plus `fixed` rows'
+//          worth each (window and tap loads, the first transforms). A
+//          workgroup that has the memory to itself takes about 3/4 of the
+//          time per row that it takes among 256;
+//   work   all rows and `halo` more per tile (history that a tile reads
+//          again), spread evenly.
+// Tiles of one height for every size (256 rows forward, 128 adjoint) left
+// most CUs idle below 65536 rows: 1024 channels, 16 taps, complex64, forward
+// 1024 rows 135 -> 12 us, 16384 rows 146 -> 60; adjoint 1024 rows 118 -> 34,
+// 16384 rows 145 -> 119. At 65536 rows and above both rules take about 256
+// rows (16-row tiles: forward 301 us against 210).
+static int tile_rows(int64_t B, int64_t rows, int rb, int64_t fixed, int64_t halo, int slots)
 {
-    const int64_t max_tiles = B * ceil_div(rows, ceil_div(min_rows, rb) * rb);
-    int64_t best_sb = ceil_div(min_rows, rb) * rb;
-    double best_eff = 0.0;
-    for (int64_t rounds = 1; rounds * cus <= max_tiles * 2 + cus; ++rounds) {
-        // tiles per stream needed for `rounds` full rounds
-        const int64_t tiles_total = rounds * cus;
-        const int64_t tiles_per_stream = ceil_div(tiles_total, B);
-        int64_t sb = ceil_div(ceil_div(rows, tiles_per_stream), rb) * rb;
-        if (sb < rb)
-            sb = rb;
-        const int64_t n = B * ceil_div(rows, sb);
-        const double eff = (double)n / (double)(ceil_div(n, cus) * cus);
-        if (sb >= min_rows && (eff > best_eff + 1e-9 || (eff >= best_eff - 1e-9 && sb > best_sb && eff > 0.97))) {
-            best_eff = eff;
+    const int64_t most = std::min(ceil_div(rows, rb), 4 * ceil_div(slots, B) + 4);
+    double best = 0.0;
+    int64_t best_sb = 0;
+    for (int64_t k = 1; k <= most; ++k) { // tiles per stream
+        const int64_t sb = ceil_div(ceil_div(rows, k), rb) * rb;
+        if (sb == best_sb || sb > INT32_MAX / 2)
+            continue;
+        const int64_t full = B * (rows / sb), last = rows % sb;
+        const int64_t rounds = ceil_div(full, slots), idle = rounds * slots - full;
+        double path = (double)rounds * (double)(sb + fixed);
+        if (last > 0 && B > idle) // the streams' short last tiles
+            path += (double)ceil_div(B - idle, slots) * (double)(last + fixed);
+        const double work = ((double)B * rows + (double)B * ceil_div(rows, sb) * halo) / slots;
+        // of equals the shorter path
+        const double cost = std::max(0.75 * path, work) + 0.15 * path;
+        if (best_sb == 0 || cost < best) {
+            best = cost;
             best_sb = sb;
         }
     }
+    if (best_sb == 0) // rows beyond 32-bit tile heights
+        best_sb = ceil_div(256, rb) * rb;
     return (int)best_sb;
+}
+
+// gx rows per fused adjoint tile: every tile transforms T - 1 halo rows
+// again and writes a tap-gradient partial. Two workgroups a CU pay at 256
+// channels only (65536 rows, 16 taps: 128-row tiles 92 us, 272-row ones 114;
+// 512 channels, 32768 rows: 64-row tiles 111, 144-row ones 102).
+static int adjoint_tile_rows(int64_t B, int64_t rows, int T, int C, int cus)
+{
+    return tile_rows(B, rows, 16, T + 10, T / 2 + 2, C <= 256 ? 2 * cus : cus);
 }
 
 // Largest tile height (a multiple of rb) whose rows plus `extra` halo rows
@@ -303,17 +327,6 @@ static int64_t row_bytes_in(const pfb_desc &d) { return (int64_t)d.channels * by
 static bool block_views_fit(int64_t row_bytes, int rows, int tp)
 {
     return row_bytes * (rows + tp) <= 0x7fffffff;
-}
-
-// Rows per fused tile: whole rounds over the workgroups that fit at once
-// (`slots`), at least 256 rows so that the T-1 halo rows a tile re-reads stay
-// a small fraction of its input (measured: 64-row tiles fetched 1.24x the
-// input bytes; their halo rows are not served by the cache, because
-// neighbouring tiles run at the same time and the halo is the start of one
-// tile's walk but the end of the other's).
-static int choose_fused_sb(const pfb_desc &d, int rb, int slots)
-{
-    return balanced_tile_rows(d.batch, d.spectra, rb, 256, slots);
 }
 
 static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
@@ -373,16 +386,14 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
                fused_supported(d->dtype, p->tp, p->log2c) &&
                !(tuned && te.path == PATH_SPLIT)) {
         p->path = PATH_FUSED;
+        // a chunk of the pipelined kernel, which takes two per loop trip
         const int rb = fused_rows_per_chunk(p->tp, p->log2c);
         if (tuned && te.fused_ws >= 0)
             p->fused_ws = te.fused_ws != 0;
-        // the wave-specialised kernel pays a pipeline fill per tile: longer
-        // tiles, balanced over the CUs
-        // workgroups per CU at once: LDS-bound (two chunk buffers of C
-        // padded complex rows and the twiddles)
-        const int slots = p->num_cus * (p->log2c >= 10 ? 1 : 2);
-        p->fused_sb = p->fused_ws ? balanced_tile_rows(d->batch, d->spectra, rb, 128, p->num_cus)
-                                  : choose_fused_sb(*d, rb, slots);
+        // LDS and registers allow one workgroup a CU at 1024 channels, two
+        // below
+        p->fused_sb = tile_rows(d->batch, d->spectra, p->fused_ws ? rb : rb / 2, 8 + d->taps / 4, d->taps / 2 + 2,
+                                p->log2c >= 10 ? p->num_cus : 2 * p->num_cus);
         if (tuned && te.fused_sb >= rb && te.fused_sb % rb == 0)
             p->fused_sb = te.fused_sb;
     } else {
@@ -409,7 +420,7 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
         // rows are processed in chunks.
         const int64_t row_bytes = (int64_t)d->channels * 8;
         if (p->path == PATH_SPLIT && !(d->flags & (PFB_NO_FUSE | PFB_PLAIN | PFB_CONVERT_PER_USE)) && p->log2c >= 0 &&
-            !p->long_fir && block_supported(d->dtype, p->tp, p->log2c, false) && block_views_fit(row_bytes_in(*d), block_rows(p->log2c, false), p->tp)) {
+            !p->long_fir && block_supported(d->dtype, p->tp, p->log2c, false)) {
             // a tuned chunk size asks for the two launches
             p->blocked = tuned && te.block >= 0 ? te.block != 0
                          : tuned && te.chunk_mib > 0
@@ -438,9 +449,7 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
         }
         if (d->dtype == PFB_C64 && d->taps <= PFB_MAX_TAPS_WINDOW) {
             p->bwd_fused = !(d->flags & (PFB_NO_FUSE | PFB_PLAIN)) && fused_bwd_supported(p->tp, p->log2c);
-            // at least 128 gx rows per tile (the T-1 halo rows are transformed
-            // twice and every tile writes a tap-gradient partial)
-            p->bwd_sb = balanced_tile_rows(d->batch, d->spectra + d->taps - 1, 16, 128, p->num_cus);
+            p->bwd_sb = adjoint_tile_rows(d->batch, d->spectra + d->taps - 1, d->taps, d->channels, p->num_cus);
             if (tuned && te.bwd_sb >= 16 && te.bwd_sb <= 65536)
                 p->bwd_sb = te.bwd_sb;
             p->bwd_sb = std::min(p->bwd_sb, view_rows_cap((int64_t)d->channels * 8, 16, 0));
@@ -944,7 +953,7 @@ pfb_status pfb_internal_fail(pfb_status st, const char *msg) { return fail(st, m
 // gx rows per fused adjoint tile, as a plan chooses it (no tuning cache)
 int pfb_internal_bwd_tile_rows(int64_t B, int64_t S, int T, int C, int cus)
 {
-    const int sb = balanced_tile_rows(B, S + T - 1, 16, 128, cus);
+    const int sb = adjoint_tile_rows(B, S + T - 1, T, C, cus);
     return std::min(sb, view_rows_cap((int64_t)C * 8, 16, 0));
 }
 pfb_status pfb_internal_validate(const pfb_desc *d, bool batched_beam) { return validate_desc(d, batched_beam); }

@@ -1,0 +1,49 @@
+"""Fused tiles of every height the tile rule gives: from one transform round
+(8 or 16 rows) at short streams to several hundred rows, with streams that end
+inside, at and just past a tile."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1511_03599_amd import synth
+from helpers import GH_TOL, GX_TOL, c128, rel_l2, say, taps_to_device, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("C,T,S,B,dtype", [
+    (1024, 16, 7, 1, "c64"), (1024, 16, 8, 2, "ci16"), (1024, 9, 9, 1, "ci8"), (1024, 4, 2049, 1, "cf16"),
+    (1024, 16, 4097, 1, "c64"), (1024, 8, 999, 17, "ci8"), (512, 16, 8, 1, "c64"), (512, 3, 17, 3, "ci16"),
+    (512, 12, 8193, 1, "c64"), (512, 8, 100, 300, "ci8"), (256, 8, 16, 1, "cf16"), (256, 16, 33, 2, "c64"),
+    (256, 5, 16385, 1, "ci8"),
+])
+def test_forward_tiles_equal_split(dev, C, T, S, B, dtype):
+    import torch
+    from paper_1511_03599_amd import pfb
+    x = synth.device_quantised_noise((B, S + T - 1, C), dtype, 2900 + C + T, dev)
+    h = taps_to_device(synth.random_taps(C, T, 2901), dev)
+    plan = pfb.Plan(C, T, S, B, dtype)
+    say(f"forward tiles C={C} T={T} S={S} B={B} {dtype}: {plan.info()['fir_rows']} rows")
+    assert plan.info()["path"] == "fused"
+    ref = pfb.Plan(C, T, S, B, dtype, pfb.NO_FUSE).execute(x, h)
+    assert torch.equal(plan.execute(x, h), ref)
+
+
+@pytest.mark.parametrize("C,T,S,B", [(1024, 16, 17, 1), (1024, 7, 600, 3), (1024, 16, 2000, 1), (512, 16, 1001, 3),
+                                     (512, 4, 29, 1), (256, 16, 1, 2), (256, 8, 3000, 2)])
+def test_adjoint_tiles(dev, C, T, S, B):
+    from paper_1511_03599_amd import pfb
+    x = synth.quantise(synth.complex_gaussian((B, S + T - 1, C), 2950 + C), "c64")
+    h = synth.random_taps(C, T, 2951)
+    gY = synth.quantise(synth.complex_gaussian((B, S, C), 2952), "c64")
+    plan = pfb.Plan(C, T, S, B, "c64")
+    rows_per_tile = plan.info()["backward_rows"]
+    say(f"adjoint tiles C={C} T={T} S={S} B={B}: {rows_per_tile} rows")
+    gx, gh = plan.backward(to_device(x, dev), taps_to_device(h, dev), to_device(gY, dev))
+    rows = sorted(r for r in {0, 1, T - 1, rows_per_tile - 1, rows_per_tile, 3 * rows_per_tile, S - 1, S + T - 2}
+                  if 0 <= r < S + T - 1)
+    gx_r = oracle.pfb_adjoint_x_rows(h, gY, rows)
+    assert max(rel_l2(c128(gx[b, rows]), gx_r[b]) for b in range(B)) <= GX_TOL
+    ch = [0, 1, C // 2, C - 1]
+    gh_r = oracle.pfb_adjoint_h_channels(x, gY, T, ch)
+    assert rel_l2(gh[:, ch].cpu().numpy().astype(np.float64), gh_r) <= GH_TOL
