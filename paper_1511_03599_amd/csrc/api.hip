@@ -312,6 +312,23 @@ static int adjoint_tile_rows(int64_t B, int64_t rows, int T, int C, int cus)
     return tile_rows(B, rows, 16, T + 10, T / 2 + 2, C <= 256 ? 2 * cus : cus);
 }
 
+// Raw spectra per wave tile of the split adjoint (one wave per 64 channels),
+// whole blocks of its unrolled loop: enough waves for twice the eight that
+// the registers allow per CU, and no more than 160 rows (128 at 32 taps, 256
+// at 64), where the history that a tile reads again is small and the waves in
+// flight still sweep a narrow band of rows. The whole adjoint at 256-row
+// tiles, as every size had, against these: 128 channels x 4000 spectra x 3
+// 141 -> 27 us, 2048 x 10000 x 3 606 -> 462, 4096 x 8192 x 2 610 -> 518.
+static int split_adjoint_rows(const pfb_desc &d, int tp, int cus)
+{
+    const int u = tp > 16 ? tp : 16, most = tp <= 16 ? 160 : tp == 32 ? 128 : 256;
+    const double waves = (double)d.batch * (double)ceil_div(d.channels, 64);
+    const double rows = waves * (double)(d.spectra + d.taps - 1) / (16.0 * cus);
+    if (rows >= most)
+        return most;
+    return (int)std::max<int64_t>(1, ceil_div((int64_t)rows, u)) * u;
+}
+
 // Largest tile height (a multiple of rb) whose rows plus `extra` halo rows
 // fit one bounded view (under 2 GiB) at row_bytes per row: the fused adjoint
 // addresses a tile's rows through such views.
@@ -466,6 +483,7 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
                 st = dev_alloc(reinterpret_cast<void **>(&p->ws_gy), p->ws_gy_bytes, "backward workspace");
                 if (st != PFB_OK)
                     return st;
+                p->gh_sb = split_adjoint_rows(*d, p->tp, p->num_cus);
                 // tiles of gh_sb filtered spectra (gh_partial_kernel) or of
                 // gh_sb raw spectra (gxgh_kernel), whichever is more
                 parts = (int64_t)d->batch * ceil_div(d->spectra + d->taps - 1, p->gh_sb);

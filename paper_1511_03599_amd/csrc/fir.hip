@@ -150,14 +150,20 @@ __global__ __launch_bounds__(256) void gh_partial_kernel(GhArgs a)
 // so gy is read once for both, and x once: 24 bytes per sample instead of
 // the 32 of the reversed-tap FIR and gh_partial_kernel run one after the
 // other. Window slot j of output p holds gy[p - (TP-1) + j], which carries
-// tap t = TP-1-j. Tiles wholly inside the stream run with unconditional
-// loads and stores, the others with tested ones.
+// tap t = TP-1-j. Every load and store goes through a bounded view, so the
+// first and last tiles of a stream and ragged channel counts run the same
+// unconditional code as the others (with a tested form for those, 128
+// channels x 4000 spectra x 3 took 33 us in its best tiles, now 27, and 294
+// spectra x 28 at 2048 channels 172, now 150). HBM-bound: 4.0 TB/s on 24
+// bytes per sample at 4096 channels, 16 taps; a prefetch of 8 rows, which
+// leaves registers for a third wave per SIMD, was no faster (518 against 510
+// us for the whole adjoint).
 template <int TP, int D>
 __global__ __launch_bounds__(256) void gxgh_kernel(GxGhArgs a)
 {
     constexpr int U = TP > D ? TP : D;
     static_assert(U % TP == 0 && U % D == 0, "static window and prefetch slots");
-    const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave_id();
+    const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave_id_uniform();
     const int64_t total = (int64_t)a.B * a.n_tiles * a.n_cchunks;
     if (gw >= total)
         return;
@@ -170,10 +176,30 @@ __global__ __launch_bounds__(256) void gxgh_kernel(GxGhArgs a)
     const int64_t rows = a.S + a.T - 1;
     const int64_t p0 = (int64_t)tile * a.SB;
     const int np = (int)((rows - p0) < a.SB ? (rows - p0) : a.SB);
-    const float2 *xb = a.x + (int64_t)b * rows * a.C + c;
-    const float2 *gb = a.gy + (int64_t)b * a.S * a.C + c;
-    float2 *gxb = a.gx + (int64_t)b * rows * a.C + c;
     const int off = TP - a.T;
+    const int rb = a.C * 8; // bytes of a row
+
+    // views of the tile's rows: x and gx rows [p0, p0 + np), gy rows
+    // [p0 - (TP-1), p0 + np) as far as they exist. A lane without a channel
+    // addresses beyond every view.
+    const int64_t q0 = p0 - (TP - 1), qv = q0 < 0 ? 0 : q0;
+    const int64_t nq = (a.S < p0 + np ? a.S : p0 + np) - qv;
+    const BufView vx = buf_view(a.x + ((int64_t)b * rows + p0) * a.C, (int64_t)np * rb);
+    const BufView vgx = buf_view(a.gx + ((int64_t)b * rows + p0) * a.C, (int64_t)np * rb);
+    const BufView vg = buf_view(a.gy + ((int64_t)b * a.S + qv) * a.C, nq * rb);
+    const int lane_off = active ? c * 8 : (int)0x80000000u;
+    int ox = lane_off;                         // row p0 in vx and vgx
+    int og = lane_off + (int)(p0 - qv) * rb;   // row p0 in vg (rows before it are negative steps)
+    auto ldx = [&](int r) PFB_INLINE {
+        float2 o[1];
+        buf_load_c64<1>(vx, ox + r * rb, o);
+        return o[0];
+    };
+    auto ldg = [&](int r) PFB_INLINE {
+        float2 o[1];
+        buf_load_c64<1>(vg, og + r * rb, o);
+        return o[0];
+    };
 
     float hp[TP];
     sfor<TP>([&](auto jc) {
@@ -184,81 +210,37 @@ __global__ __launch_bounds__(256) void gxgh_kernel(GxGhArgs a)
     sfor<TP>([&](auto j) { acc[j] = 0.0f; });
     float2 w[TP];
     float2 pg[D], px[D];
-
-    // output row o = base + jj of the tile: gy row p0 + o enters the window,
-    // x row p0 + o is consumed, gx row p0 + o is computed
-    auto step = [&](auto jjc, float2 g_new, float2 xv, float2 &g_out) PFB_INLINE {
-        constexpr int jj = decltype(jjc)::value;
-        w[(jj + TP - 1) % TP] = g_new;
-        float gr = 0.0f, gi = 0.0f;
-        sfor<TP>([&](auto jc) PFB_INLINE {
-            constexpr int j = decltype(jc)::value;
-            const float2 v = w[(jj + j) % TP];
-            gr = __builtin_fmaf(hp[j], v.x, gr);
-            gi = __builtin_fmaf(hp[j], v.y, gi);
-            acc[j] = __builtin_fmaf(v.x, xv.x, __builtin_fmaf(v.y, xv.y, acc[j]));
-        });
-        g_out = make_float2(gr, gi);
-    };
-
-    const bool clean = (cch + 1) * 64 <= a.C && np == a.SB && np % U == 0 && p0 - (TP - 1) >= 0 &&
-                       p0 + np <= a.S;
-    if (clean) {
-        sfor<TP - 1>([&](auto k) PFB_INLINE { w[k] = gb[(p0 - (TP - 1) + k) * a.C]; });
-        sfor<D>([&](auto k) PFB_INLINE {
-            pg[k] = gb[(p0 + k) * a.C];
-            px[k] = xb[(p0 + k) * a.C];
-        });
-        // FULL blocks prefetch D rows ahead for every row (the next block
-        // exists and D <= U); the LAST block only where that stays inside
-        auto block = [&](int base, auto lastc) PFB_INLINE {
-            constexpr bool LASTB = decltype(lastc)::value;
-            sfor<U>([&](auto jjc) PFB_INLINE {
-                constexpr int jj = decltype(jjc)::value;
-                const int64_t p = p0 + base + jj;
-                const float2 g_new = pg[jj % D], xv = px[jj % D];
-                if constexpr (!LASTB || jj + D < U) {
-                    pg[jj % D] = gb[(p + D) * a.C];
-                    px[jj % D] = xb[(p + D) * a.C];
-                }
-                float2 g;
-                step(jjc, g_new, xv, g);
-                store_nt(gxb + p * a.C, g);
+    // issued in the order they are used: a wait inside the loop also covers
+    // the first pass, and counts from the order of these loads
+    sfor<TP - 1>([&](auto k) PFB_INLINE { w[k] = ldg(decltype(k)::value - (TP - 1)); });
+    __builtin_amdgcn_sched_barrier(0);
+    sfor<D>([&](auto k) PFB_INLINE {
+        pg[k] = ldg(decltype(k)::value);
+        px[k] = ldx(decltype(k)::value);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    // output row base + jj of the tile: gy row p0 + base + jj enters the
+    // window, x row p0 + base + jj is consumed, that gx row is computed
+    for (int base = 0; base < np; base += U) {
+        sfor<U>([&](auto jjc) PFB_INLINE {
+            constexpr int jj = decltype(jjc)::value;
+            const float2 xv = px[jj % D];
+            w[(jj + TP - 1) % TP] = pg[jj % D];
+            pg[jj % D] = ldg(jj + D);
+            px[jj % D] = ldx(jj + D);
+            float gr = 0.0f, gi = 0.0f;
+            sfor<TP>([&](auto jc) PFB_INLINE {
+                constexpr int j = decltype(jc)::value;
+                const float2 v = w[(jj + j) % TP];
+                gr = __builtin_fmaf(hp[j], v.x, gr);
+                gi = __builtin_fmaf(hp[j], v.y, gi);
+                acc[j] = __builtin_fmaf(v.x, xv.x, __builtin_fmaf(v.y, xv.y, acc[j]));
             });
-        };
-        int base = 0;
-        for (; base + U < np; base += U)
-            block(base, std::false_type{});
-        block(base, std::true_type{});
-    } else {
-        auto ldg = [&](int64_t q) -> float2 {
-            return (active && q >= 0 && q < a.S) ? gb[q * a.C] : make_float2(0.0f, 0.0f);
-        };
-        auto ldx = [&](int64_t p) -> float2 { return (active && p < rows) ? xb[p * a.C] : make_float2(0.0f, 0.0f); };
-        sfor<TP - 1>([&](auto k) { w[k] = ldg(p0 - (TP - 1) + k); });
-        sfor<D>([&](auto k) {
-            if (k < np) {
-                pg[k] = ldg(p0 + k);
-                px[k] = ldx(p0 + k);
-            }
+            const float2 g[1] = {make_float2(gr, gi)};
+            buf_store_c64_nt<1>(vgx, ox + jj * rb, g);
         });
-        for (int base = 0; base < np; base += U) {
-            sfor<U>([&](auto jjc) {
-                constexpr int jj = decltype(jjc)::value;
-                const int o = base + jj;
-                if (o < np) {
-                    const float2 g_new = pg[jj % D], xv = px[jj % D];
-                    if (o + D < np) {
-                        pg[jj % D] = ldg(p0 + o + D);
-                        px[jj % D] = ldx(p0 + o + D);
-                    }
-                    float2 g;
-                    step(jjc, g_new, xv, g);
-                    if (active)
-                        store_nt(gxb + (p0 + o) * a.C, g);
-                }
-            });
-        }
+        ox += U * rb;
+        og += U * rb;
     }
     if (active) {
         float *pb = a.part + ((int64_t)b * a.n_tiles + tile) * (int64_t)a.T * a.C + c;

@@ -47,3 +47,21 @@ def test_adjoint_tiles(dev, C, T, S, B):
     ch = [0, 1, C // 2, C - 1]
     gh_r = oracle.pfb_adjoint_h_channels(x, gY, T, ch)
     assert rel_l2(gh[:, ch].cpu().numpy().astype(np.float64), gh_r) <= GH_TOL
+
+
+@pytest.mark.parametrize("C,T,S,B", [(128, 16, 1, 1), (64, 9, 15, 2), (32, 3, 700, 3), (128, 5, 4000, 1), (2048, 17, 33, 2),
+                                     (96, 31, 200, 2), (4096, 8, 170, 1), (1000, 12, 90, 1)])
+def test_split_adjoint_tiles(dev, C, T, S, B):
+    """Tiles of one unrolled block and more, ragged last tiles and channel
+    counts that are no multiple of a wave."""
+    from paper_1511_03599_amd import pfb
+    say(f"split adjoint tiles C={C} T={T} S={S} B={B}")
+    x = synth.quantise(synth.complex_gaussian((B, S + T - 1, C), 2970 + C), "c64")
+    h = synth.random_taps(C, T, 2971)
+    gY = synth.quantise(synth.complex_gaussian((B, S, C), 2972), "c64")
+    plan = pfb.Plan(C, T, S, B, "c64")
+    assert plan.info()["backward_kind"] == "split"
+    gx, gh = plan.backward(to_device(x, dev), taps_to_device(h, dev), to_device(gY, dev))
+    gx_r, gh_r = oracle.pfb_adjoint(x, h, gY)
+    assert rel_l2(c128(gx), gx_r) <= GX_TOL
+    assert rel_l2(gh.cpu().numpy().astype(np.float64), gh_r) <= GH_TOL
