@@ -340,10 +340,11 @@ static int view_rows_cap(int64_t row_bytes, int rb, int extra)
 
 static int64_t row_bytes_in(const pfb_desc &d) { return (int64_t)d.channels * bytes_per_sample(d.dtype); }
 
-// The blocked kernel addresses a block's raw rows through one bounded view.
-static bool block_views_fit(int64_t row_bytes, int rows, int tp)
+// The blocked kernel addresses a block's raw rows, and its spectra, through
+// one bounded view each.
+static bool block_views_fit(const pfb_desc &d, int rows, int tp)
 {
-    return row_bytes * (rows + tp) <= 0x7fffffff;
+    return row_bytes_in(d) * (rows + tp) <= 0x7fffffff && (int64_t)d.channels * 8 * rows <= 0x7fffffff;
 }
 
 static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
@@ -777,7 +778,7 @@ extern "C" pfb_status pfb_plan_create_vegas(int32_t channels, int32_t subbands, 
         p->vegas_log2cv = l2;
         st = make_twiddles(l2, &p->twiddle);
         p->blocked = !p->long_fir && block_pays(dtype, p->tp, l2, true, subbands, spectra) &&
-                     block_views_fit(row_bytes_in(d), block_rows(l2, true), p->tp);
+                     block_views_fit(d, block_rows(l2, true), p->tp);
     }
     if (st == PFB_OK && !p->blocked) {
         p->ws_y_bytes = spectra * cols * 8;

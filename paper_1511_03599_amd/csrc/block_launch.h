@@ -31,8 +31,8 @@
 // VALU issues 64% of the time (86 operations per sample). Measured against
 // FIR + FFT launches (2^27 samples, 16 taps): 4096 channels int8 0.66 -> 0.40
 // ms, complex64 0.78 -> 0.52; 2048 channels complex64 0.79 -> 0.50; 1024
-// channels, 32 taps, 2^26 samples 0.40 -> 0.28; 8 sub-bands of 4096 channels,
-// int8, 2^27 samples 0.92 -> 0.44. With H = 1: 0.49, 0.65, 0.53, 0.29, 0.60.
+// channels, 32 taps, 2^26 samples 0.40 -> 0.27; 8 sub-bands of 4096 channels,
+// int8, 2^27 samples 0.92 -> 0.42. With H = 1: 0.49, 0.65, 0.53, 0.29, 0.60.
 // Two workgroups of half the rows and threads per CU, which would overlap
 // their phases, read more through L2 and were slower (4096 channels int8
 // 0.48, complex64 0.68 with H = 2). Blocks dealt to the XCDs one by one
@@ -132,9 +132,13 @@ __device__ __forceinline__ void block_transform(const BlockArgs &a, float2 *lds,
     using S = typename K::S;
     using BF = typename K::BF;
     const int t = (int)threadIdx.x;
-    // first spectrum row in Y and values between the rows' spectra
-    float2 *Y = POL ? a.Y + (s0 * a.nsub + unit) * (2 * C) : a.Y + (unit * a.S + s0) * C;
-    const int64_t ystep = POL ? a.nsub * (2 * C) : (int64_t)C;
+    // the view of the rows' spectra, and bytes between them; spectra from
+    // `nout` on lie outside it, so every store is issued unconditionally and
+    // the next block's first rows are waited for without waiting for the
+    // stores issued after them
+    const int ystep = (int)(POL ? a.nsub * (2 * C) : (int64_t)C) * 8;
+    const BufView vy = buf_view(POL ? a.Y + (s0 * a.nsub + unit) * (2 * C) : a.Y + (unit * a.S + s0) * C,
+                                (int64_t)(nout - 1) * ystep + (POL ? 2 * C : C) * 8);
     if constexpr (K::BIG) {
         constexpr int R = BF::R, RR = BF::RR, Q = BF::Q, RSTEP = R + R / 16;
         constexpr int SUBS = K::TROWS * Q, AT = NT / R;
@@ -179,14 +183,12 @@ __device__ __forceinline__ void block_transform(const BlockArgs &a, float2 *lds,
                     sfor<Q - 1>([&](auto i) PFB_INLINE { v[pc][i + 1] = cmul(v[pc][i + 1], tw2[jc][i]); });
                     Dft<Q>::run(v[pc]);
                 });
-                if (rp < nout) {
-                    float2 *out = Y + rp * ystep + PR * j;
-                    sfor<Q>([&](auto i) PFB_INLINE {
-                        float2 o[PR];
-                        sfor<PR>([&](auto pc) PFB_INLINE { o[pc] = v[pc][i]; });
-                        store_c64_nt<PR>(out + decltype(i)::value * PR * RR, o);
-                    });
-                }
+                const int o = rp * ystep + j * (PR * 8);
+                sfor<Q>([&](auto i) PFB_INLINE {
+                    float2 z[PR];
+                    sfor<PR>([&](auto pc) PFB_INLINE { z[pc] = v[pc][i]; });
+                    buf_store_c64_nt<PR>(vy, o + decltype(i)::value * PR * RR * 8, z);
+                });
             });
         });
     } else {
@@ -197,8 +199,7 @@ __device__ __forceinline__ void block_transform(const BlockArgs &a, float2 *lds,
             const int tr = round * K::NG + gid;
             float2 *row = lds + tr * K::ROW;
             const int sr = POL ? tr / 2 : tr;
-            const bool valid = sr < nout;
-            float2 *out = Y + sr * ystep + (POL ? tr % 2 : 0);
+            const int o = sr * ystep + (POL ? tr % 2 * 8 : 0);
             int ln = t % G;
             asm volatile("" : "+v"(ln));
             float2 v[S::E];
@@ -206,9 +207,9 @@ __device__ __forceinline__ void block_transform(const BlockArgs &a, float2 *lds,
                 fft_gather_first_lds<LOG2C, G>(ln, row, v);
             else
                 fft_gather_first<LOG2C, G>(ln, [&](int idx) { return row[S::pad(idx)]; }, v);
-            fft_passes<LOG2C, G, false, true, true>(ln, row, tws, v, [&](int idx, float2 o) {
-                if (valid)
-                    store_nt(out + (POL ? 2 * idx : idx), o);
+            fft_passes<LOG2C, G, false, true, true>(ln, row, tws, v, [&](int idx, float2 z) {
+                const float2 z1[1] = {z};
+                buf_store_c64_nt<1>(vy, o + idx * (POL ? 16 : 8), z1);
             });
         }
     }
@@ -304,7 +305,13 @@ __global__ __launch_bounds__(BLOCK_NT) void block_kernel(BlockArgs a)
     int voff = voff_of(0, first);
     sfor<TP>([&](auto j) PFB_INLINE { load_tap(j, hoff_of(0)); });
     static_assert(D <= L, "ring depth");
-    sfor<D>([&](auto i) PFB_INLINE { buf_load_packed<DT, V>(vx, voff + decltype(i)::value * rb, pf[i]); });
+    // issued in the order of their use: a wait inside the loop counts from
+    // the order of the loads on every path to it
+    __builtin_amdgcn_sched_barrier(0);
+    sfor<D>([&](auto i) PFB_INLINE {
+        buf_load_packed<DT, V>(vx, voff + decltype(i)::value * rb, pf[i]);
+        __builtin_amdgcn_sched_barrier(0);
+    });
 
     for (;;) {
         const int64_t qn = q + grid;
@@ -330,6 +337,12 @@ __global__ __launch_bounds__(BLOCK_NT) void block_kernel(BlockArgs a)
             sfor<LP>([&](auto ic) PFB_INLINE {
                 constexpr int i = decltype(ic)::value;
                 float2 xv[V];
+                // loads stay in the order they are waited for, and in step
+                // with the sums (free to move, they gathered at the end of
+                // a pass: 1024 channels, 32 taps 0.281 -> 0.266 ms, 8
+                // sub-bands 0.438 -> 0.417)
+                if constexpr (i % 2 == 0)
+                    __builtin_amdgcn_sched_barrier(0);
                 if constexpr (i < L)
                     unpack<DT, V>(pf[i % D], xv);
                 if constexpr (i + D < L)
@@ -372,10 +385,10 @@ __global__ __launch_bounds__(BLOCK_NT) void block_kernel(BlockArgs a)
                 fir_pass(p);
         }
         const int nrows = (int)(a.S - cur.s0 < R2 ? a.S - cur.s0 : R2);
+        // left at the end of an iteration only: every path to the next block
+        // then issues stores after that block's prefetched rows
 #pragma unroll 1
-        for (int half = 0; half < H; ++half) {
-            if (half * R >= nrows)
-                break;
+        for (int half = 0;;) {
             if constexpr (H > 1) {
                 if (half == 1) {
                     lds_barrier(); // the first half's transforms are done
@@ -388,8 +401,10 @@ __global__ __launch_bounds__(BLOCK_NT) void block_kernel(BlockArgs a)
                 }
             }
             lds_barrier();
-            block_transform<K, JPT, POL, LOG2C>(a, lds, tws, tw2, cur.unit, cur.s0 + half * R,
-                                                nrows - half * R < R ? nrows - half * R : R);
+            const int left = nrows - half * R;
+            block_transform<K, JPT, POL, LOG2C>(a, lds, tws, tw2, cur.unit, cur.s0 + half * R, left < R ? left : R);
+            if (++half == H || half * R >= nrows)
+                break;
         }
         lds_barrier(); // the LDS rows are free for the next block
         if (!more)
