@@ -131,19 +131,25 @@ struct pfb_plan {
 // Twiddles
 // ----------------------------------------------------------------------------
 
-// exp(-2 pi i m / C) for m < C (mixed-radix transforms), FP64 rounded once.
-static pfb_status make_twiddles_mixed(int C, float2 **out)
+// Twiddles of a mixed-radix schedule, W_{RL}^{ik} laid out [i][k] per pass
+// after the first (FP64, rounded once).
+static pfb_status make_twiddles_mixed(const GfftSched &g, float2 **out)
 {
-    std::vector<float2> host((size_t)C);
-    for (int m = 0; m < C; ++m) {
-        const double a = -2.0 * M_PI * (double)m / (double)C;
-        host[(size_t)m] = make_float2((float)std::cos(a), (float)std::sin(a));
+    const size_t n = (size_t)g.tw_entries;
+    std::vector<float2> host(n);
+    for (int p = 1; p < g.npass; ++p) {
+        const int R = g.pass[p].radix, L = g.pass[p].stride, RL = R * L;
+        for (int i = 0; i < R; ++i)
+            for (int k = 0; k < L; ++k) {
+                const double a = -2.0 * M_PI * (double)(((int64_t)i * k) % RL) / (double)RL;
+                host[(size_t)(g.pass[p].tw + i * L + k)] = make_float2((float)std::cos(a), (float)std::sin(a));
+            }
     }
     void *p = nullptr;
-    hipError_t e = hipMalloc(&p, sizeof(float2) * (size_t)C);
+    hipError_t e = hipMalloc(&p, sizeof(float2) * n);
     if (e != hipSuccess)
         return fail(PFB_E_NOMEM, std::string("hipMalloc(twiddles): ") + hipGetErrorString(e));
-    e = hipMemcpy(p, host.data(), sizeof(float2) * (size_t)C, hipMemcpyHostToDevice);
+    e = hipMemcpy(p, host.data(), sizeof(float2) * n, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(p);
         return hip_fail(e, "hipMemcpy(twiddles)");
@@ -424,7 +430,7 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
             p->mixed = true;
             if (!gfft_schedule(d->channels, &p->gf))
                 return fail(PFB_E_UNSUPPORTED, "no radix schedule for this channel count");
-            st = make_twiddles_mixed(d->channels, &p->twiddle);
+            st = make_twiddles_mixed(p->gf, &p->twiddle);
         } else {
             st = make_twiddles(p->log2c, &p->twiddle);
         }

@@ -41,7 +41,12 @@ __global__ __launch_bounds__(FftKernelShape<LOG2C>::NT, FftKernelShape<LOG2C>::M
     float2 *out = a.out + g * a.out_gstride + r * C;
     fft_run<LOG2C, G, INV, false>(
         lane, lds + gid * S::PADDED, a.tw, [&](int idx) { return in[idx]; },
-        [&](int idx, float2 v) { store_nt(out + idx, v); });
+        [&](int idx, float2 v) {
+            if constexpr (G >= 16)
+                store_nt(out + idx, v);
+            else // less than a line at a time: L2 gathers it
+                out[idx] = v;
+        });
 }
 
 // Transforms of C >= 4096 points: persistent workgroups of one transform

@@ -2,29 +2,42 @@
 // (C = 2^a 3^b 5^c 7^d): the DFT of Sec. 2, Eq. (2), unnormalised, natural
 // bin order; the inverse (exp(+...)) as conjugate in, conjugate out.
 //
-// Stockham autosort, one pass per radix of C's factorisation (powers of two
-// as radix 16, 8, 4, 2 first, then 7, 5, 3). A pass of radix R and stride L
-// (the product of the earlier radices) lets butterfly j (0 <= j < C/R) read
-// elements j + i*C/R, multiply element i by W_{RL}^{ik} (k = j mod L), run an
-// R-point DFT and write element i to (j - k) R + k + i L. The row lives in
-// LDS in two buffers used alternately (the passes are out of place), the
-// lanes of a group stride over the butterflies, and the row is loaded and
-// stored coalesced. Twiddles come from one table exp(-2 pi i m / C),
-// m < C, computed in FP64 on the host: W_{RL}^{ik} = table[i k C/(RL)].
+// Stockham autosort, one pass per radix of the schedule. A pass of radix R
+// and stride L (the product of the earlier radices) lets butterfly j
+// (0 <= j < C/R) read elements j + i*C/R, multiply element i by W_{RL}^{ik}
+// (k = j mod L), run an R-point DFT and write element i to
+// (j - k) R + k + i L. The first pass reads the row from HBM and the last
+// writes it there, both coalesced; in between the row lives in one padded LDS
+// buffer: a lane holds the inputs of all its butterflies before any lane
+// writes. Twiddles come from a table per pass
+// laid out [i][k], so that neighbouring lanes read neighbouring entries.
 //
-// A group of G lanes owns one row: G = 64 (one wave, several rows per block,
-// no block barriers) up to C = 1024, G = 256 (one row per block) up to 4096,
-// G = 512 above. The two LDS buffers of a row limit how many rows a CU
-// holds, so the larger rows take more lanes to keep enough waves in flight
-// (T=16, 2^27 samples: 1536 channels 1.32 -> 1.03 ms with 256 lanes instead
-// of 64; 6144 channels 1.65 -> 1.36 ms and 7168 1.58 -> 1.32 ms with 512
-// instead of 256; 768 channels stay faster with 64).
+// Radices up to 16, composites of coprime factors (6, 10, 12, 14, 15) by the
+// prime-factor map, so without inner twiddles: 3072 channels take three
+// passes (16, 16, 12), 1344 three (14, 12, 8), 6144 four (12, 8, 8, 8). With
+// the factors 16, 8, 4, 2, 7, 5, 3 one by one (3072: 16, 16, 4, 3), two LDS
+// buffers per row, unpadded, and a division by L in the lane, the transforms
+// of 2^27 samples took 686 us at 3072 channels (now 432, 5.0 TB/s), 952 at
+// 6144 (478) and 608 at 1536 (433). Bound: HBM and, above 4096 channels, the
+// barriers of a fourth pass.
+//
+// A group of G lanes owns one row: as many as the pass with the most
+// butterflies per gf_butterflies(R) asks for, rounded to a power of two up to
+// a wave (several rows per block of 256 lanes), to whole waves above (one row
+// per block). Groups of fewer than 16 lanes write less than a line at a time
+// and store through L2 (96 channels, 2^20 spectra: non-temporal 935 us, plain
+// 389; from 16 lanes on non-temporal is the faster, 240 channels 286 to 303).
 #include <algorithm>
 
 #include "fft_device.h"
 #include "launch.h"
 
 namespace pfb {
+
+// Butterflies of radix R per lane, at most: one from radix 9 up (two of 15
+// with their twiddles would take all registers of two waves per SIMD), up to
+// 16 elements below.
+constexpr int gf_butterflies(int R) { return R > 8 ? 1 : 16 / R; }
 
 // cos(2 pi m / R) and sin(2 pi m / R) for the odd radices.
 template <int R> struct OddTw;
@@ -81,127 +94,228 @@ template <int R> __device__ __forceinline__ void dft_odd(float2 *v)
     sfor<R>([&](auto i) PFB_INLINE { v[i] = out[i]; });
 }
 
+template <int R> __device__ __forceinline__ void dft_any(float2 *v);
+
+constexpr int inverse_mod(int a, int n)
+{
+    for (int x = 1; x < n; ++x)
+        if (a * x % n == 1)
+            return x;
+    return 0;
+}
+
+// N1 * N2 points, N1 and N2 coprime: with n = N2 n1 + N1 n2 and
+// k = N2 (N2^-1 mod N1) k1 + N1 (N1^-1 mod N2) k2 (all mod N1 N2),
+// W_N^{nk} = W_N1^{n1 k1} W_N2^{n2 k2}.
+template <int N1, int N2> __device__ __forceinline__ void dft_pfa(float2 *v)
+{
+    constexpr int N = N1 * N2, E1 = N2 * inverse_mod(N2 % N1, N1), E2 = N1 * inverse_mod(N1 % N2, N2);
+    float2 a[N2][N1];
+    sfor<N2>([&](auto n2) PFB_INLINE {
+        sfor<N1>([&](auto n1) PFB_INLINE {
+            a[n2][n1] = v[(N2 * decltype(n1)::value + N1 * decltype(n2)::value) % N];
+        });
+        dft_any<N1>(a[n2]);
+    });
+    sfor<N1>([&](auto k1) PFB_INLINE {
+        float2 b[N2];
+        sfor<N2>([&](auto n2) PFB_INLINE { b[n2] = a[n2][k1]; });
+        dft_any<N2>(b);
+        sfor<N2>([&](auto k2) PFB_INLINE {
+            v[(E1 * decltype(k1)::value + E2 * decltype(k2)::value) % N] = b[k2];
+        });
+    });
+}
+
 template <int R> __device__ __forceinline__ void dft_any(float2 *v)
 {
     if constexpr (R == 3 || R == 5 || R == 7)
         dft_odd<R>(v);
+    else if constexpr (R == 6)
+        dft_pfa<2, 3>(v);
+    else if constexpr (R == 10)
+        dft_pfa<2, 5>(v);
+    else if constexpr (R == 12)
+        dft_pfa<4, 3>(v);
+    else if constexpr (R == 14)
+        dft_pfa<2, 7>(v);
+    else if constexpr (R == 15)
+        dft_pfa<3, 5>(v);
     else
         Dft<R>::run(v);
 }
 
-template <int G> __device__ __forceinline__ void gf_sync()
+// Place of element idx in the row's LDS buffer.
+__device__ __forceinline__ int gf_pad(int idx) { return idx + (idx >> 4); }
+
+// Element idx of a row at a (wave-uniform) base: a 32-bit offset per lane.
+template <class T> __device__ __forceinline__ T &gf_at(T *base, uint32_t idx)
 {
-    if constexpr (G > 64) {
-        lds_barrier();
-    } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
+    return *(T *)((__attribute__((address_space(1))) char *)(uintptr_t)base + idx * 8u);
 }
 
-// One pass: `src(idx)` returns input element idx, `dst(idx, v)` takes output
-// element idx (LDS rows between passes; the row in global memory for the
-// first pass's inputs and the last pass's outputs, both coalesced).
-template <int R, int G, class Src, class Dst>
-__device__ __forceinline__ void gf_pass(Src &&src, Dst &&dst, int C, int L, const float2 *tw, int lane)
+// One pass of radix R over the row; MULTI: the group spans several waves.
+template <int R, bool FIRST, bool LAST, bool INV, bool MULTI>
+__device__ __forceinline__ void gf_pass(const GfftPass ps, int C, int G, int lane, const float2 *in, float2 *out,
+                                        float2 *row, const float2 *tw)
 {
-    const int CR = C / R;
-    const int tstep = C / (R * L);
-    for (int j = lane; j < CR; j += G) {
-        const int k = j % L;
-        float2 v[R];
-        sfor<R>([&](auto i) PFB_INLINE { v[i] = src(j + decltype(i)::value * CR); });
-        if (L > 1) {
-            sfor<R - 1>([&](auto ic) PFB_INLINE {
-                constexpr int i = decltype(ic)::value + 1;
-                v[i] = cmul(v[i], tw[i * k * tstep]);
-            });
+    constexpr int NB = gf_butterflies(R); // C/R <= NB * G
+    const int CR = C / R, L = ps.stride;
+    float2 v[NB][R];
+    int o[NB];
+    sfor<NB>([&](auto q) PFB_INLINE {
+        const int j = lane + G * decltype(q)::value;
+        if (j < CR) {
+            if constexpr (FIRST) {
+                o[q] = j * R;
+                sfor<R>([&](auto i) PFB_INLINE {
+                    const float2 z = gf_at(in, (uint32_t)(j + decltype(i)::value * CR));
+                    v[q][i] = INV ? conj2(z) : z;
+                });
+            } else {
+                const int k = j - (int)__umulhi((uint32_t)j, ps.magic) * L;
+                o[q] = (j - k) * R + k;
+                float2 w[R];
+                sfor<R - 1>([&](auto i) PFB_INLINE { w[i + 1] = gf_at(tw, (uint32_t)(ps.tw + k + (decltype(i)::value + 1) * L)); });
+                sfor<R>([&](auto i) PFB_INLINE { v[q][i] = row[gf_pad(j + decltype(i)::value * CR)]; });
+                sfor<R - 1>([&](auto i) PFB_INLINE { v[q][i + 1] = cmul(v[q][i + 1], w[i + 1]); });
+            }
+            dft_any<R>(v[q]);
+            if constexpr (LAST) // (j - k) R + k is j: L R = C
+                sfor<R>([&](auto i) PFB_INLINE {
+                    float2 *d = &gf_at(out, (uint32_t)(j + decltype(i)::value * CR));
+                    const float2 z = INV ? conj2(v[q][i]) : v[q][i];
+                    if (MULTI || G >= 16)
+                        store_nt(d, z);
+                    else // less than a line at a time: L2 gathers it
+                        *d = z;
+                });
         }
-        dft_any<R>(v);
-        const int o = (j - k) * R + k;
-        sfor<R>([&](auto i) PFB_INLINE { dst(o + decltype(i)::value * L, v[i]); });
+        // one butterfly's addresses and twiddles at a time in registers
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    if constexpr (!LAST) {
+        if constexpr (!FIRST)
+            group_sync<MULTI ? 128 : 64>(); // every lane has read before any lane writes
+        sfor<NB>([&](auto q) PFB_INLINE {
+            if (lane + G * decltype(q)::value < CR)
+                sfor<R>([&](auto i) PFB_INLINE { row[gf_pad(o[q] + decltype(i)::value * L)] = v[q][i]; });
+        });
+        group_sync<MULTI ? 128 : 64>();
     }
 }
 
-// Pass p of the schedule with radix R (runtime), from src to dst.
-template <int G, class Src, class Dst>
-__device__ __forceinline__ void gf_pass_any(int R, Src &&src, Dst &&dst, int C, int L, const float2 *tw, int lane)
+template <bool FIRST, bool LAST, bool INV, bool MULTI>
+__device__ __forceinline__ void gf_pass_any(const GfftPass ps, int C, int G, int lane, const float2 *in, float2 *out,
+                                            float2 *row, const float2 *tw)
 {
-    switch (R) {
-    case 16: gf_pass<16, G>(src, dst, C, L, tw, lane); break;
-    case 8: gf_pass<8, G>(src, dst, C, L, tw, lane); break;
-    case 4: gf_pass<4, G>(src, dst, C, L, tw, lane); break;
-    case 2: gf_pass<2, G>(src, dst, C, L, tw, lane); break;
-    case 7: gf_pass<7, G>(src, dst, C, L, tw, lane); break;
-    case 5: gf_pass<5, G>(src, dst, C, L, tw, lane); break;
-    default: gf_pass<3, G>(src, dst, C, L, tw, lane); break;
+#define PFB_GF(R)                                                                                            \
+    case R: gf_pass<R, FIRST, LAST, INV, MULTI>(ps, C, G, lane, in, out, row, tw); break;
+    switch (ps.radix) {
+        PFB_GF(16)
+        PFB_GF(15)
+        PFB_GF(14)
+        PFB_GF(12)
+        PFB_GF(10)
+        PFB_GF(8)
+        PFB_GF(7)
+        PFB_GF(6)
+        PFB_GF(5)
+        PFB_GF(4)
+        PFB_GF(3)
+    default:
+        gf_pass<2, FIRST, LAST, INV, MULTI>(ps, C, G, lane, in, out, row, tw);
     }
+#undef PFB_GF
 }
 
-template <int G, bool INV>
-__global__ __launch_bounds__((G > 256 ? G : 256)) void gfft_kernel(FftArgs a, GfftSched s)
+// MAXT: threads per block at most (256: groups within a wave).
+template <bool INV, int MAXT>
+__global__ __launch_bounds__(MAXT) void gfft_kernel(FftArgs a, GfftSched s)
 {
+    constexpr bool MULTI = MAXT > 256;
     extern __shared__ float2 gf_lds[];
-    const int C = s.C;
-    const int grp = (int)threadIdx.x / G;
-    const int lane = (int)threadIdx.x % G;
-    const int64_t row = (int64_t)blockIdx.x * s.rows_per_block + grp;
-    // With G = 64 the groups are waves and use no block barrier, so a group
-    // past the last row may leave; with G = 256 there is one row per block.
-    if (row >= a.nrows)
+    const int C = s.C, G = s.group;
+    const int grp = MULTI ? 0 : (int)threadIdx.x / G;
+    const int lane = MULTI ? (int)threadIdx.x : (int)threadIdx.x % G;
+    const int64_t r0 = (int64_t)blockIdx.x * s.rows_per_block + grp;
+    // MULTI: one row per block, so the exit is block-uniform; otherwise a
+    // group past the last row may leave, there is no block barrier
+    if (r0 >= a.nrows)
         return;
-    const int64_t g = row / a.rows_per_group, r = row % a.rows_per_group;
+    const int64_t g = r0 / a.rows_per_group, r = r0 % a.rows_per_group;
     const float2 *in = a.in + g * a.in_gstride + r * C;
     float2 *out = a.out + g * a.out_gstride + r * C;
-    float2 *A = gf_lds + (size_t)grp * 2 * C;
-    float2 *B = A + C;
-    auto lds_src = [&](const float2 *buf) { return [buf](int idx) { return buf[idx]; }; };
-    auto lds_dst = [&](float2 *buf) { return [buf](int idx, float2 v) { buf[idx] = v; }; };
-    // the first pass reads the row from global memory and the last writes it
-    // there (the schedule always has at least two passes: C >= 32, radix <= 16)
-    gf_pass_any<G>(
-        s.radix[0], [&](int idx) { const float2 v = in[idx]; return INV ? conj2(v) : v; }, lds_dst(A), C, 1, a.tw,
-        lane);
-    gf_sync<G>();
-    int L = s.radix[0];
+    float2 *row = gf_lds + grp * (C + C / 16 + 1);
+    gf_pass_any<true, false, INV, MULTI>(s.pass[0], C, G, lane, in, out, row, a.tw);
     for (int p = 1; p + 1 < s.npass; ++p) {
-        gf_pass_any<G>(s.radix[p], lds_src(A), lds_dst(B), C, L, a.tw, lane);
-        float2 *t = A;
-        A = B;
-        B = t;
-        L *= s.radix[p];
-        gf_sync<G>();
+        // opaque: every radix's addresses would be hoisted out of the loop
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        gf_pass_any<false, false, INV, MULTI>(s.pass[p], C, G, ln, in, out, row, a.tw);
     }
-    gf_pass_any<G>(
-        s.radix[s.npass - 1], lds_src(A), [&](int idx, float2 v) { store_nt(out + idx, INV ? conj2(v) : v); }, C, L,
-        a.tw, lane);
+    gf_pass_any<false, true, INV, MULTI>(s.pass[s.npass - 1], C, G, lane, in, out, row, a.tw);
 }
 
-// Radix schedule of a 7-smooth C (false if C has another prime factor or
-// needs more passes than GfftSched holds).
+// The fewest radices whose product is `rem`, none above `most`; of those the
+// smallest sum (the flattest schedule). Returns the count, or 0.
+static int gfft_factor(int rem, int most, int depth, int *best, int *best_sum, int sum, int *cur, int n, int found)
+{
+    if (rem == 1) {
+        if (found == 0 || n < found || (n == found && sum < *best_sum)) {
+            std::copy(cur, cur + n, best);
+            *best_sum = sum;
+            return n;
+        }
+        return found;
+    }
+    if (n == depth || (found && n + 1 > found))
+        return found;
+    for (int r : {16, 15, 14, 12, 10, 8, 7, 6, 5, 4, 3, 2})
+        if (r <= most && rem % r == 0) {
+            cur[n] = r;
+            found = gfft_factor(rem / r, r, depth, best, best_sum, sum + r, cur, n + 1, found);
+        }
+    return found;
+}
+
+// Radix schedule of a 7-smooth C (false if C has another prime factor).
 bool gfft_schedule(int C, GfftSched *s)
 {
+    if (C < 17 || C > 8192)
+        return false; // the kernel's first and last passes are distinct
+    int radix[GF_MAX_PASS], cur[GF_MAX_PASS], sum = 0;
+    const int np = gfft_factor(C, 16, GF_MAX_PASS, radix, &sum, 0, cur, 0, 0);
+    if (np < 2)
+        return false;
     GfftSched t{};
     t.C = C;
-    int rem = C, np = 0;
-    for (int r : {16, 8, 4, 2, 7, 5, 3}) {
-        while (rem % r == 0) {
-            if (np >= GF_MAX_PASS)
-                return false;
-            t.radix[np++] = r;
-            rem /= r;
-        }
-    }
-    if (rem != 1 || np < 2) // the kernel's first and last passes are distinct
-        return false;
     t.npass = np;
-    t.group = C <= 1024 ? 64 : C <= 4096 ? 256 : 512;
-    const int64_t row_lds = (int64_t)2 * C * 8;
-    int f = 1;
-    if (t.group == 64)
-        f = (int)std::max<int64_t>(1, std::min<int64_t>(4, 65536 / row_lds));
-    t.rows_per_block = f;
+    int L = 1;
+    for (int p = 0; p < np; ++p) {
+        GfftPass &q = t.pass[p];
+        q.radix = radix[p];
+        q.stride = L;
+        q.magic = (uint32_t)((((uint64_t)1 << 32) + (uint64_t)L - 1) / (uint64_t)L); // 0 for L = 1, unused
+        q.tw = t.tw_entries;
+        if (p > 0)
+            t.tw_entries += radix[p] * L;
+        L *= radix[p];
+    }
+    int lanes = 1;
+    for (int p = 0; p < np; ++p) {
+        const int per = radix[p] * gf_butterflies(radix[p]);
+        lanes = std::max(lanes, (C + per - 1) / per);
+    }
+    if (lanes <= 64) {
+        t.group = 1;
+        while (t.group < lanes)
+            t.group *= 2;
+        t.rows_per_block = 256 / t.group;
+    } else {
+        t.group = (lanes + 63) / 64 * 64;
+        t.rows_per_block = 1;
+    }
     *s = t;
     return true;
 }
@@ -211,24 +325,16 @@ hipError_t launch_gfft(const FftArgs &a, const GfftSched &s, bool inv, hipStream
     const int64_t blocks = (a.nrows + s.rows_per_block - 1) / s.rows_per_block;
     if (blocks <= 0)
         return hipSuccess;
-    const size_t lds = (size_t)s.rows_per_block * 2 * s.C * sizeof(float2);
+    const size_t lds = (size_t)s.rows_per_block * (s.C + s.C / 16 + 1) * sizeof(float2);
     const dim3 grid((unsigned)blocks), block((unsigned)(s.group * s.rows_per_block));
-    if (s.group == 64) {
-        auto k = inv ? gfft_kernel<64, true> : gfft_kernel<64, false>;
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)lds);
-        hipLaunchKernelGGL(k, grid, block, lds, st, a, s);
-    } else if (s.group == 256) {
-        auto k = inv ? gfft_kernel<256, true> : gfft_kernel<256, false>;
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)lds);
-        hipLaunchKernelGGL(k, grid, block, lds, st, a, s);
-    } else {
-        auto k = inv ? gfft_kernel<512, true> : gfft_kernel<512, false>;
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)lds);
-        hipLaunchKernelGGL(k, grid, block, lds, st, a, s);
-    }
+    auto k = s.group <= 64   ? (inv ? gfft_kernel<true, 256> : gfft_kernel<false, 256>)
+             : s.group <= 512 ? (inv ? gfft_kernel<true, 512> : gfft_kernel<false, 512>)
+                              : (inv ? gfft_kernel<true, 1024> : gfft_kernel<false, 1024>);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(k, grid, block, lds, st, a, s);
     return hipGetLastError();
 }
 

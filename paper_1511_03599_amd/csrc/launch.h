@@ -126,13 +126,20 @@ hipError_t launch_fft_pol2(const FftArgs &a, int log2c, hipStream_t st);
 hipError_t launch_vegas_taps(const float *in, float *out, int T, int cv, int nsub, hipStream_t st);
 
 // Mixed-radix transform for C = 2^a 3^b 5^c 7^d (not a power of two).
-constexpr int GF_MAX_PASS = 16;
+constexpr int GF_MAX_PASS = 8;
+struct GfftPass {
+    int radix;
+    int stride;          // product of the earlier radices
+    uint32_t magic;      // j / stride = (j * magic) >> 32 for j < 8192 (stride > 1)
+    int tw;              // first twiddle W_{radix*stride}^{ik}, laid out [i][k]
+};
 struct GfftSched {
     int C;
     int npass;
-    int group;           // lanes per row: 64, 256 or 512
+    int group;           // lanes per row
     int rows_per_block;
-    int radix[GF_MAX_PASS];
+    int tw_entries;
+    GfftPass pass[GF_MAX_PASS];
 };
 bool gfft_schedule(int C, GfftSched *s);
 hipError_t launch_gfft(const FftArgs &a, const GfftSched &s, bool inv, hipStream_t st);

@@ -1,4 +1,4 @@
-"""Fused tiles of every height the tile rule gives: from one transform round
+"""Tiles and transform schedules of every shape the size rules give. Fused tiles of every height the tile rule gives: from one transform round
 (8 or 16 rows) at short streams to several hundred rows, with streams that end
 inside, at and just past a tile."""
 import numpy as np
@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_1511_03599_amd import synth
-from helpers import GH_TOL, GX_TOL, c128, rel_l2, say, taps_to_device, to_device
+from helpers import GH_TOL, GX_TOL, SPEC_TOL, c128, rel_l2, say, taps_to_device, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -62,6 +62,26 @@ def test_split_adjoint_tiles(dev, C, T, S, B):
     plan = pfb.Plan(C, T, S, B, "c64")
     assert plan.info()["backward_kind"] == "split"
     gx, gh = plan.backward(to_device(x, dev), taps_to_device(h, dev), to_device(gY, dev))
+    gx_r, gh_r = oracle.pfb_adjoint(x, h, gY)
+    assert rel_l2(c128(gx), gx_r) <= GX_TOL
+    assert rel_l2(gh.cpu().numpy().astype(np.float64), gh_r) <= GH_TOL
+
+
+# schedules with every radix, every group width (4 lanes to 13 waves) and a
+# row count that leaves a block part empty
+@pytest.mark.parametrize("C,S", [(36, 7), (45, 70), (50, 3), (54, 65), (63, 5), (162, 33), (240, 17), (280, 9), (6000, 3),
+                                 (8000, 2), (8100, 2), (7203, 3)])
+def test_mixed_radix_schedules(dev, C, S):
+    from paper_1511_03599_amd import pfb
+    T, B = 3, 2
+    say(f"mixed-radix schedule C={C} S={S}")
+    x = synth.quantise(synth.complex_gaussian((B, S + T - 1, C), 2980 + C), "c64")
+    h = synth.random_taps(C, T, 2981)
+    gY = synth.quantise(synth.complex_gaussian((B, S, C), 2982), "c64")
+    plan = pfb.Plan(C, T, S, B, "c64")
+    args = (to_device(x, dev), taps_to_device(h, dev))
+    assert rel_l2(c128(plan.execute(*args)), oracle.pfb_forward(x, h)) <= SPEC_TOL
+    gx, gh = plan.backward(*args, to_device(gY, dev))
     gx_r, gh_r = oracle.pfb_adjoint(x, h, gY)
     assert rel_l2(c128(gx), gx_r) <= GX_TOL
     assert rel_l2(gh.cpu().numpy().astype(np.float64), gh_r) <= GH_TOL
