@@ -255,10 +255,11 @@ pfb_status pfb_backward_noalloc(const pfb_desc *desc, const void *x, const float
 
 /*
  * Many independent beams with their own C, T, S (one stream each, complex
- * float32, C a power of two in [32, 8192], T <= PFB_MAX_TAPS_WINDOW) in one
- * persistent launch
- * per call, recorded into a HIP graph when the plan is created. Each beam's
- * result is the forward filter bank of its descriptor (Alg. 1 then Eq. (2)),
+ * float32, C a power of two in [32, 8192], T <= PFB_MAX_TAPS_WINDOW). Beams
+ * too small to fill the GPU share one persistent launch per call, recorded
+ * into a HIP graph when the plan is created; large ones run as launches of
+ * their own where that is faster, on the same stream. Each beam's result is
+ * the forward filter bank of its descriptor (Alg. 1 then Eq. (2)),
  * bit-identical to a separate single-beam plan.
  *   nbeams  >= 1; beams: host array of nbeams descriptors (batch must be 1,
  *           dtype C64; flags ignored)
@@ -273,9 +274,9 @@ pfb_status pfb_plan_create_batched(int32_t nbeams, const pfb_desc *beams, pfb_pl
 /*
  * Execute a batched plan.
  *   x, taps, Y: HOST arrays of nbeams DEVICE pointers, beam i laid out as a
- *   single stream of its own descriptor. The pointer values are baked into
- *   the plan's graph on the first call; later calls with different pointers
- *   rebuild the device-side pointer table (no allocation).
+ *   single stream of its own descriptor. The persistent launch reads them
+ *   from a device-side table, which calls with different pointers rebuild
+ *   (no allocation).
  */
 pfb_status pfb_execute_batched(pfb_plan *plan, const void *const *x, const float *const *taps,
                                void *const *Y, void *stream);

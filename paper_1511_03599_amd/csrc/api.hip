@@ -309,6 +309,15 @@ static int tile_rows(int64_t B, int64_t rows, int rb, int64_t fixed, int64_t hal
     return (int)best_sb;
 }
 
+// Filtered spectra per fused tile: whole chunks, of which the pipelined
+// kernel takes two per loop trip. LDS and registers allow one workgroup a CU
+// at 1024 channels, two below.
+static int fused_tile_rows(int64_t B, int64_t S, int T, int log2c, int cus, bool ws)
+{
+    const int rb = fused_rows_per_chunk(padded_taps(T), log2c);
+    return tile_rows(B, S, ws ? rb : rb / 2, 8 + T / 4, T / 2 + 2, log2c >= 10 ? cus : 2 * cus);
+}
+
 // gx rows per fused adjoint tile: every tile transforms T - 1 halo rows
 // again and writes a tap-gradient partial. Two workgroups a CU pay at 256
 // channels only (65536 rows, 16 taps: 128-row tiles 92 us, 272-row ones 114;
@@ -410,14 +419,10 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
                fused_supported(d->dtype, p->tp, p->log2c) &&
                !(tuned && te.path == PATH_SPLIT)) {
         p->path = PATH_FUSED;
-        // a chunk of the pipelined kernel, which takes two per loop trip
         const int rb = fused_rows_per_chunk(p->tp, p->log2c);
         if (tuned && te.fused_ws >= 0)
             p->fused_ws = te.fused_ws != 0;
-        // LDS and registers allow one workgroup a CU at 1024 channels, two
-        // below
-        p->fused_sb = tile_rows(d->batch, d->spectra, p->fused_ws ? rb : rb / 2, 8 + d->taps / 4, d->taps / 2 + 2,
-                                p->log2c >= 10 ? p->num_cus : 2 * p->num_cus);
+        p->fused_sb = fused_tile_rows(d->batch, d->spectra, d->taps, p->log2c, p->num_cus, p->fused_ws);
         if (tuned && te.fused_sb >= rb && te.fused_sb % rb == 0)
             p->fused_sb = te.fused_sb;
     } else {
@@ -975,6 +980,11 @@ extern "C" const char *pfb_last_error(void) { return g_last_error.c_str(); }
 
 // Internal hooks for the batched and tuning modules.
 pfb_status pfb_internal_fail(pfb_status st, const char *msg) { return fail(st, msg); }
+// Rows per fused forward tile, as a plan chooses it (no tuning cache)
+int pfb_internal_fused_tile_rows(int64_t B, int64_t S, int T, int log2c, int cus)
+{
+    return fused_tile_rows(B, S, T, log2c, cus, false);
+}
 // gx rows per fused adjoint tile, as a plan chooses it (no tuning cache)
 int pfb_internal_bwd_tile_rows(int64_t B, int64_t S, int T, int C, int cus)
 {

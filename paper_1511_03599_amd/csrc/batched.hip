@@ -1,7 +1,9 @@
 // Batched multi-beam filter bank: many independent beams, each with its own
-// C, T and S, processed by ONE persistent kernel launch per call.
+// C, T and S. Beams too small to fill the chip share ONE persistent kernel
+// launch per call; large ones run as launches of the fused or blocked forward
+// where those apply (BT_ALONE_SAMPLES), in the same stream.
 //
-// Work is a table of tiles built on the host when the plan is created. A tile
+// The persistent kernel's work is a table of tiles built on the host when the plan is created. A tile
 // is a run of consecutive filtered spectra of one beam, over all of its
 // channels. A persistent workgroup takes the next tile from an atomic counter
 // and does all of the tile's work itself:
@@ -48,6 +50,7 @@ constexpr int BT_WAVES = BT_THREADS / 64;
 constexpr int BT_TASK_ROWS = 32;         // filtered spectra per FIR wave task
 constexpr int BT_LDS = 8704;             // float2: the largest transform round (one 8192-point row)
 constexpr int BT_MAX_TAPS = PFB_MAX_TAPS_WINDOW;
+constexpr int64_t BT_ALONE_SAMPLES = 1 << 22; // filtered samples from which a beam has a launch of its own
 
 struct BeamInfo {
     const float2 *tw;      // twiddles for C
@@ -258,6 +261,10 @@ struct Batched {
     int nbeams = 0;
     std::vector<pfb_desc> descs;
     std::vector<BeamInfo> info;         // host copy (pointers to device memory)
+    std::vector<int> fused_rows;        // beams with launches of their own: rows per fused tile, 0 for the blocked
+                                        // kernel; -1: a beam of the persistent kernel
+    int n_alone = 0;
+    int num_cus = 256;
     BeamInfo *d_info = nullptr;
     BeamPtrs *d_ptrs = nullptr;
     BeamPtrs *h_ptrs = nullptr;         // pinned staging for the pointer table
@@ -348,6 +355,13 @@ static pfb_status build_batched(int32_t nbeams, const pfb_desc *beams, Batched *
     B->descs.assign(beams, beams + nbeams);
     B->info.resize((size_t)nbeams);
     const int tile_kib = batched_tile_kib(nbeams, beams);
+    int dev = 0;
+    hipDeviceProp_t prop;
+    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess &&
+        prop.multiProcessorCount > 0)
+        B->num_cus = prop.multiProcessorCount;
+    B->fused_rows.assign((size_t)nbeams, -1);
+    double rest = 0.0; // samples of the persistent kernel's beams
     float2 *tw_by_log2c[14] = {};
     for (int i = 0; i < nbeams; ++i) {
         const pfb_desc &d = beams[i];
@@ -370,6 +384,41 @@ static pfb_status build_batched(int32_t nbeams, const pfb_desc *beams, Batched *
             B->allocs.push_back(tw_by_log2c[bi.log2c]);
         }
         bi.tw = tw_by_log2c[bi.log2c];
+        // A beam that fills the chip by itself runs as a launch of the fused
+        // or blocked forward, whose filtered spectra stay on the chip; the
+        // persistent kernel's go through its slot. The launch's ramp and tail
+        // cost some 10 us, what a quarter of the samples at the line take.
+        // (64 uneven beams of 2.1 G samples 12.8 -> 10.9 ms, 6 of 80 M 0.84
+        // -> 0.44.)
+        // Long windows at 2048 channels and more gain less, on 4 M samples
+        // nothing (4096 channels, 32 taps, 10 beams of 4 M 392 -> 447 us;
+        // other sizes 258 -> 155, 269 -> 190, 436 -> 276).
+        const int64_t line = bi.TP >= 32 && bi.log2c >= 11 ? 4 * BT_ALONE_SAMPLES : BT_ALONE_SAMPLES;
+        if (d.spectra * d.channels >= line) {
+            if (fused_supported(DT_C64, bi.TP, bi.log2c))
+                B->fused_rows[(size_t)i] = pfb_internal_fused_tile_rows(1, d.spectra, d.taps, bi.log2c, B->num_cus);
+            else if (block_pays(DT_C64, bi.TP, bi.log2c, false, 1, d.spectra))
+                B->fused_rows[(size_t)i] = 0;
+        }
+        if (B->fused_rows[(size_t)i] >= 0)
+            ++B->n_alone;
+        else
+            rest += (double)d.spectra * d.channels;
+    }
+    if (B->n_alone == nbeams)
+        return PFB_OK; // no persistent launch
+    // Tables of little work get tiles of few rows, down to four, so that the
+    // workgroups (two a CU) share it: 16 beams of 8 M samples in all, up to
+    // 8192 channels, 506 -> 294 us. Not for less than half the rows, which
+    // read their history again more often (10 beams of 4096 channels and 32
+    // taps, 4 M samples each, 20 rows for 32: 392 -> 427 us).
+    for (int i = 0; i < nbeams; ++i) {
+        BeamInfo &bi = B->info[(size_t)i];
+        if (B->fused_rows[(size_t)i] >= 0)
+            continue;
+        const double even = rest / (2.0 * B->num_cus) / bi.C;
+        if (even <= bi.tile_rows / 2)
+            bi.tile_rows = std::max(4, (int)even / 4 * 4);
         B->slot_elems = std::max<int64_t>(B->slot_elems, (int64_t)bi.tile_rows * bi.C);
     }
 
@@ -388,6 +437,8 @@ static pfb_status build_batched(int32_t nbeams, const pfb_desc *beams, Batched *
     std::vector<TileDesc> tiles;
     for (int bidx : order) {
         const BeamInfo &bi = B->info[(size_t)bidx];
+        if (B->fused_rows[(size_t)bidx] >= 0)
+            continue;
         for (int64_t r0 = 0; r0 < bi.S; r0 += bi.tile_rows) {
             TileDesc t{};
             t.beam = bidx;
@@ -401,15 +452,11 @@ static pfb_status build_batched(int32_t nbeams, const pfb_desc *beams, Batched *
         return pfb_internal_fail(PFB_E_UNSUPPORTED, "batched tile table too large");
     B->ntiles = (int)tiles.size();
 
-    int dev = 0, cus = 256;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-        cus = prop.multiProcessorCount;
     int per_cu = 1;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batched_kernel, BT_THREADS, 0) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
-    B->grid = std::min(cus * per_cu, B->ntiles);
+    B->grid = std::min(B->num_cus * per_cu, B->ntiles);
 
     if (hipMalloc(&B->d_info, sizeof(BeamInfo) * (size_t)nbeams) != hipSuccess ||
         hipMalloc(&B->d_ptrs, sizeof(BeamPtrs) * (size_t)nbeams) != hipSuccess ||
@@ -513,6 +560,41 @@ extern "C" pfb_status pfb_execute_batched(pfb_plan *p, const void *const *x, con
             return pfb_internal_fail(PFB_E_INVALID, "device pointers must be 16-byte aligned");
     }
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    for (int i = 0; i < B->nbeams; ++i) {
+        const int sb = B->fused_rows[(size_t)i];
+        if (sb < 0)
+            continue;
+        const BeamInfo &bi = B->info[(size_t)i];
+        hipError_t e;
+        if (sb > 0) {
+            FusedArgs a{};
+            a.x = x[i];
+            a.h = taps[i];
+            a.Y = reinterpret_cast<float2 *>(Y[i]);
+            a.tw = bi.tw;
+            a.T = bi.T;
+            a.B = 1;
+            a.SB = sb;
+            a.n_tiles = (int)((bi.S + sb - 1) / sb);
+            a.S = bi.S;
+            e = launch_fused(a, DT_C64, bi.TP, bi.log2c, st);
+        } else {
+            BlockArgs a{};
+            a.x = x[i];
+            a.h = taps[i];
+            a.Y = reinterpret_cast<float2 *>(Y[i]);
+            a.tw = bi.tw;
+            a.T = bi.T;
+            a.num_cus = B->num_cus;
+            a.S = bi.S;
+            a.units = 1;
+            e = launch_block(a, DT_C64, bi.TP, bi.log2c, false, st);
+        }
+        if (e != hipSuccess)
+            return pfb_internal_fail(PFB_E_HIP, (std::string("beam launch: ") + hipGetErrorString(e)).c_str());
+    }
+    if (B->n_alone == B->nbeams)
+        return PFB_OK;
     bool changed = false;
     for (int i = 0; i < B->nbeams; ++i) {
         const BeamPtrs &op = B->last_ptrs[(size_t)i];

@@ -117,3 +117,26 @@ def test_batched_tuner_writes_cache(dev, tmp_path):
     assert f[1] == "batched" and int(f[2]) == 2 and int(f[3]) == 1024 * 2000 + 256 * 4000
     kib = int(f[4].split("=")[1])
     assert kib in (64, 128, 256, 512, 1024, 2048, 4096)
+
+
+@pytest.mark.parametrize("beams", [
+    # beams with launches of their own (fused, blocked) beside ones of the
+    # persistent kernel; then a table of those alone; then one of little work
+    # (tiles of few rows)
+    [(1024, 16, 4097), (64, 3, 65537), (8192, 4, 513), (2048, 32, 8193), (256, 4, 100)],
+    [(512, 12, 8200), (128, 32, 32769)],
+    [(8192, 16, 65), (4096, 33, 9), (32, 64, 3)],
+])
+def test_batched_routes_equal_plain_launches(dev, beams):
+    import torch
+    from paper_1511_03599_amd import pfb
+    say(f"batched routes {beams}")
+    xs = [synth.device_noise((S + T - 1, C), 3000 + i, dev) for i, (C, T, S) in enumerate(beams)]
+    hs = [taps_to_device(synth.random_taps(C, T, 3100 + i), dev) for i, (C, T, S) in enumerate(beams)]
+    bp = pfb.BatchedPlan(beams)
+    for rep in range(2):
+        Ys = bp.execute(xs, hs)
+        for i, (C, T, S) in enumerate(beams):
+            ref = pfb.Plan(C, T, S, 1, "c64", pfb.PLAIN).execute(xs[i][None], hs[i])
+            assert torch.equal(Ys[i], ref[0]), (rep, i)
+        xs = [x.flip(0).contiguous() for x in xs]  # new buffers
