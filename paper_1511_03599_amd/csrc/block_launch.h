@@ -209,7 +209,12 @@ __device__ __forceinline__ void block_transform(const BlockArgs &a, float2 *lds,
                 fft_gather_first<LOG2C, G>(ln, [&](int idx) { return row[S::pad(idx)]; }, v);
             fft_passes<LOG2C, G, false, true, true>(ln, row, tws, v, [&](int idx, float2 z) {
                 const float2 z1[1] = {z};
-                buf_store_c64_nt<1>(vy, o + idx * (POL ? 16 : 8), z1);
+                if constexpr (G >= 16 && !POL) {
+                    buf_store_c64_nt<1>(vy, o + idx * 8, z1);
+                } else { // less than a line at a time: L2 gathers it
+                    const v2u_t w = {__float_as_uint(z.x), __float_as_uint(z.y)};
+                    __builtin_amdgcn_raw_buffer_store_b64(w, vy.r, o + idx * (POL ? 16 : 8), 0, 0);
+                }
             });
         }
     }
