@@ -724,14 +724,19 @@ extern "C" pfb_status pfb_execute_stream(pfb_plan *p, void *xbuf, const float *t
     const int64_t stream_bytes = (d.spectra + d.taps - 1) * row_bytes; // per stream in xbuf
     const int64_t head = (int64_t)(d.taps - 1) * row_bytes;           // carried rows per stream
     char *xb = static_cast<char *>(xbuf);
+    // With at least T-1 new spectra the last T-1 rows are the caller's own,
+    // so they can be carried before the filter bank runs, by the launch that
+    // fills the headroom.
+    const bool rotate = d.spectra >= d.taps - 1;
     if (head > 0) {
         // carried spectra into the headroom rows
-        hipError_t e = launch_copy_blocks(p->hist, head, xb, stream_bytes, head, d.batch, st);
+        hipError_t e = rotate ? launch_rotate_history(p->hist, xb, stream_bytes, d.spectra * row_bytes, head, d.batch, st)
+                              : launch_copy_blocks(p->hist, head, xb, stream_bytes, head, d.batch, st);
         if (e != hipSuccess)
             return hip_fail(e, "streaming history copy-in");
     }
     pfb_status r = pfb_execute(p, xbuf, taps, y, Y, stream);
-    if (r != PFB_OK || head == 0)
+    if (r != PFB_OK || head == 0 || rotate)
         return r;
     // the last T-1 rows of every stream become the carried spectra
     hipError_t e = launch_copy_blocks(xb + d.spectra * row_bytes, stream_bytes, p->hist, head, head, d.batch, st);

@@ -167,6 +167,11 @@ hipError_t launch_fused_ws(const FusedArgs &a, int dtype, int tp, int log2c, hip
 // (src NULL: zeros).
 hipError_t launch_copy_blocks(const void *src, int64_t src_stride, void *dst, int64_t dst_stride, int64_t bytes,
                               int64_t nblk, hipStream_t st);
+// Streaming history of nblk streams: head rows <- hist, hist <- tail rows, in
+// one launch. `bytes` per stream, head at xb + b*stride, tail at head + tail;
+// head and tail must not overlap.
+hipError_t launch_rotate_history(void *hist, char *xb, int64_t stride, int64_t tail, int64_t bytes, int64_t nblk,
+                                 hipStream_t st);
 bool fused_supported(int dtype, int tp, int log2c);
 hipError_t launch_fused_bwd(const BwdArgs &a, int tp, int log2c, hipStream_t st);
 hipError_t launch_fused_bwd_ws(const BwdArgs &a, int tp, int log2c, hipStream_t st);
