@@ -105,13 +105,24 @@ def make_desc(channels, taps, spectra, batch=1, dtype="c64", flags=0) -> Desc:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    """The HIP stream's handle; by default torch's current one on the current
+    device, read without building a Stream object (2.6 us of a call that
+    takes 10)."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+def _ready(t, dtype, shape) -> bool:
+    """A dense CUDA tensor of this type and shape: what the checks below
+    accept, in one expression (they say what is wrong with anything else, and
+    accept a few forms more)."""
+    return (isinstance(t, torch.Tensor) and t.dtype == dtype and t.shape == shape and t.is_cuda
+            and t.is_contiguous() and not t.is_conj() and not t.is_neg())
 
 
 def dtype_of(x: torch.Tensor) -> str:
@@ -176,6 +187,11 @@ class Plan:
         h = ctypes.c_void_p()
         check(lib().pfb_plan_create(ctypes.byref(d), ctypes.byref(h)))
         self._h = h
+        # the usual forms of a call's arguments
+        lead = (self.B, self.S + self.T - 1, self.C)
+        self._x_form = (torch.complex64, lead) if dtype == "c64" else (STORAGE_DTYPES[dtype], lead + (2,))
+        self._h_form = (torch.float32, (self.T, self.C))
+        self._out_form = (torch.complex64, (self.B, self.S, self.C))
 
     @property
     def rows(self):
@@ -191,31 +207,41 @@ class Plan:
                 "fused_ws": bool(i.fused_ws), "backward_rows": i.backward_rows}
 
     def _check_x(self, x):
-        check_samples(x, self.B, self.rows, self.C, self.dtype)
+        if not _ready(x, *self._x_form):
+            check_samples(x, self.B, self.rows, self.C, self.dtype)
 
-    def _check_h(self, h, device=None):
-        check_array(h, "taps", (self.T, self.C), torch.float32, device=device)
+    def _check_h(self, h, device):
+        if not (_ready(h, *self._h_form) and h.device == device):
+            check_array(h, "taps", (self.T, self.C), torch.float32, device=device)
 
     def _check_out(self, t, name, device):
-        check_array(t, name, (self.B, self.S, self.C), torch.complex64, device=device)
+        if not (_ready(t, *self._out_form) and t.device == device):
+            check_array(t, name, (self.B, self.S, self.C), torch.complex64, device=device)
 
     def execute(self, x, h, Y=None, y=None, stream=None):
         """Forward pass. Returns Y (or y for a FIR-only plan)."""
+        return self._forward(lib().pfb_execute, x, h, Y, y, stream)
+
+    def _forward(self, entry, x, h, Y, y, stream):
         self._check_x(x)
-        self._check_h(h, x.device)
-        out_shape = (self.B, self.S, self.C)
+        device = x.device
+        self._check_h(h, device)
         if y is not None:
-            self._check_out(y, "y", x.device)
+            self._check_out(y, "y", device)
+        dtype, shape = self._out_form
         if self.flags & FIR_ONLY:
             if y is None:
-                y = torch.empty(out_shape, dtype=torch.complex64, device=x.device)
-            check(lib().pfb_execute(self._h, _ptr(x), _ptr(h), _ptr(y), None, _stream(stream)))
-            return y
-        if Y is None:
-            Y = torch.empty(out_shape, dtype=torch.complex64, device=x.device)
+                y = torch.empty(shape, dtype=dtype, device=device)
+            status = entry(self._h, x.data_ptr(), h.data_ptr(), y.data_ptr(), None, _stream(stream))
+            Y = y
         else:
-            self._check_out(Y, "Y", x.device)
-        check(lib().pfb_execute(self._h, _ptr(x), _ptr(h), _ptr(y), _ptr(Y), _stream(stream)))
+            if Y is None:
+                Y = torch.empty(shape, dtype=dtype, device=device)
+            else:
+                self._check_out(Y, "Y", device)
+            status = entry(self._h, x.data_ptr(), h.data_ptr(), _ptr(y), Y.data_ptr(), _stream(stream))
+        if status != PFB_OK:
+            check(status)
         return Y
 
     def stream_buffer(self, device=None) -> torch.Tensor:
@@ -233,22 +259,7 @@ class Plan:
         overwritten with the spectra carried from the previous call."""
         if not self.flags & STREAMING:
             raise PFBError(PFB_E_STATE, "execute_stream needs a plan created with STREAMING")
-        self._check_x(xbuf)
-        self._check_h(h, xbuf.device)
-        out_shape = (self.B, self.S, self.C)
-        if y is not None:
-            self._check_out(y, "y", xbuf.device)
-        if self.flags & FIR_ONLY:
-            if y is None:
-                y = torch.empty(out_shape, dtype=torch.complex64, device=xbuf.device)
-            check(lib().pfb_execute_stream(self._h, _ptr(xbuf), _ptr(h), _ptr(y), None, _stream(stream)))
-            return y
-        if Y is None:
-            Y = torch.empty(out_shape, dtype=torch.complex64, device=xbuf.device)
-        else:
-            self._check_out(Y, "Y", xbuf.device)
-        check(lib().pfb_execute_stream(self._h, _ptr(xbuf), _ptr(h), _ptr(y), _ptr(Y), _stream(stream)))
-        return Y
+        return self._forward(lib().pfb_execute_stream, xbuf, h, Y, y, stream)
 
     def reset_stream(self, stream=None):
         """Forget the carried spectra (the next call starts from zeros)."""
@@ -259,7 +270,8 @@ class Plan:
         Returns (gx, gh); either is None when not requested."""
         if self.dtype != "c64":
             raise PFBError(PFB_E_UNSUPPORTED, "backward needs a complex64 plan")
-        check_array(gY, "gY", (self.B, self.S, self.C), torch.complex64)
+        if not _ready(gY, *self._out_form):
+            check_array(gY, "gY", (self.B, self.S, self.C), torch.complex64)
         dev = gY.device
         self._check_h(h, dev)
         if want_gh or x is not None:
