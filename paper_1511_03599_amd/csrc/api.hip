@@ -309,13 +309,23 @@ static int tile_rows(int64_t B, int64_t rows, int rb, int64_t fixed, int64_t hal
     return (int)best_sb;
 }
 
+// Largest tile height (a multiple of rb) whose rows plus `extra` halo rows
+// fit one bounded view (under 2 GiB) at row_bytes per row: the fused adjoint
+// addresses a tile's rows through such views.
+static int view_rows_cap(int64_t row_bytes, int rb, int extra)
+{
+    const int64_t cap = ((int64_t)0x7fffffff / row_bytes - extra) / rb * rb;
+    return (int)(cap < rb ? rb : (cap > INT32_MAX ? INT32_MAX / rb * rb : cap));
+}
+
 // Filtered spectra per fused tile: whole chunks, of which the pipelined
 // kernel takes two per loop trip. LDS and registers allow one workgroup a CU
 // at 1024 channels, two below.
 static int fused_tile_rows(int64_t B, int64_t S, int T, int log2c, int cus, bool ws)
 {
     const int rb = fused_rows_per_chunk(padded_taps(T), log2c);
-    return tile_rows(B, S, ws ? rb : rb / 2, 8 + T / 4, T / 2 + 2, log2c >= 10 ? cus : 2 * cus);
+    const int sb = tile_rows(B, S, ws ? rb : rb / 2, 8 + T / 4, T / 2 + 2, log2c >= 10 ? cus : 2 * cus);
+    return std::min(sb, view_rows_cap((int64_t)8 << log2c, rb, T));
 }
 
 // gx rows per fused adjoint tile: every tile transforms T - 1 halo rows
@@ -342,15 +352,6 @@ static int split_adjoint_rows(const pfb_desc &d, int tp, int cus)
     if (rows >= most)
         return most;
     return (int)std::max<int64_t>(1, ceil_div((int64_t)rows, u)) * u;
-}
-
-// Largest tile height (a multiple of rb) whose rows plus `extra` halo rows
-// fit one bounded view (under 2 GiB) at row_bytes per row: the fused adjoint
-// addresses a tile's rows through such views.
-static int view_rows_cap(int64_t row_bytes, int rb, int extra)
-{
-    const int64_t cap = ((int64_t)0x7fffffff / row_bytes - extra) / rb * rb;
-    return (int)(cap < rb ? rb : (cap > INT32_MAX ? INT32_MAX / rb * rb : cap));
 }
 
 static int64_t row_bytes_in(const pfb_desc &d) { return (int64_t)d.channels * bytes_per_sample(d.dtype); }
@@ -424,7 +425,7 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
             p->fused_ws = te.fused_ws != 0;
         p->fused_sb = fused_tile_rows(d->batch, d->spectra, d->taps, p->log2c, p->num_cus, p->fused_ws);
         if (tuned && te.fused_sb >= rb && te.fused_sb % rb == 0)
-            p->fused_sb = te.fused_sb;
+            p->fused_sb = std::min(te.fused_sb, view_rows_cap((int64_t)d->channels * 8, rb, d->taps));
     } else {
         p->path = PATH_SPLIT;
     }
