@@ -287,10 +287,10 @@ static int tile_rows(int64_t B, int64_t rows, int rb, int64_t fixed, int64_t hal
     const int64_t most = std::min(ceil_div(rows, rb), 4 * ceil_div(slots, B) + 4);
     double best = 0.0;
     int64_t best_sb = 0;
-    for (int64_t k = 1; k <= most; ++k) { // tiles per stream
+    auto consider = [&](int64_t k) { // k tiles per stream
         const int64_t sb = ceil_div(ceil_div(rows, k), rb) * rb;
         if (sb == best_sb || sb > INT32_MAX / 2)
-            continue;
+            return;
         const int64_t full = B * (rows / sb), last = rows % sb;
         const int64_t rounds = ceil_div(full, slots), idle = rounds * slots - full;
         double path = (double)rounds * (double)(sb + fixed);
@@ -303,7 +303,17 @@ static int tile_rows(int64_t B, int64_t rows, int rb, int64_t fixed, int64_t hal
             best = cost;
             best_sb = sb;
         }
-    }
+    };
+    // the shortest tiles, counts 3% apart, and those that just fill one to
+    // four rounds
+    for (int64_t m = 1; m <= 16; ++m)
+        if (ceil_div(rows, m * rb) <= most)
+            consider(ceil_div(rows, m * rb));
+    for (int64_t k = 1; k <= most; k += std::max<int64_t>(1, k / 32))
+        consider(k);
+    for (int64_t r = 1; r <= 4; ++r)
+        for (int64_t k = std::max<int64_t>(1, r * slots / B - 4); k <= std::min(most, r * slots / B + 1); ++k)
+            consider(k);
     if (best_sb == 0) // rows beyond 32-bit tile heights
         best_sb = ceil_div(256, rb) * rb;
     return (int)best_sb;
@@ -398,10 +408,21 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
     const bool cpt2_ok = p->tp <= 16 && d->channels % 2 == 0;
     const bool wide_one = (d->dtype == PFB_C64 && d->channels >= 2048) || (d->dtype == PFB_CI8 && d->channels >= 4096);
     p->fir_cpt = cpt2_ok && !wide_one ? 2 : 1;
+    // Integer input at 32 taps runs its unconditional block on tiles of one
+    // block only (several would not fit the registers), so 32 rows where
+    // every lane has a channel: 1024 channels, 65536 spectra int8 256 -> 178
+    // us, int16 286 -> 191; 96 channels 245 -> 271, so not there.
+    const bool ints = d->dtype == PFB_CI8 || d->dtype == PFB_CI16;
     p->fir_sb = p->tp >= 64                                          ? 64
-                : p->tp == 32                                        ? 128
+                : p->tp == 32                                        ? (ints && d->channels % 64 == 0 ? 32 : 128)
                 : (d->dtype == PFB_CI8 && p->tp == 16 && !wide_one) ? 64
                                                                      : 32;
+    // Launches of fewer waves than fit at once (eight a CU): shorter tiles
+    // (1024 channels, 16 taps, 1000 spectra 9.3 -> 7.0 us; 32 taps, 2000
+    // spectra 51 -> 14). A plan with a tuned entry keeps the heights above.
+    const double waves_per_row = (double)d->batch * (double)ceil_div(d->channels, 64 * p->fir_cpt);
+    if (!tuned && p->tp <= 32 && waves_per_row * (double)ceil_div(d->spectra, p->fir_sb) < 8.0 * p->num_cus)
+        p->fir_sb = p->tp <= 16 ? 16 : 32;
     if (tuned) {
         if (te.fir_cpt == 1 || (te.fir_cpt == 2 && cpt2_ok))
             p->fir_cpt = te.fir_cpt;
