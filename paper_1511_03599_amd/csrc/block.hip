@@ -33,28 +33,32 @@ int block_rows(int log2c, bool pol)
 }
 
 // Whether the blocked kernel is the faster one for `units` streams (or
-// sub-bands) of S spectra. A block takes one CU 9 us (up to 512 channels) to
-// 30 us, and a launch of few blocks leaves the other CUs idle, where the FIR
-// and FFT launches spread over more of them. Measured, split -> blocked:
-// 2048 channels, 16 taps, complex64, 32 blocks 14.6 -> 23.1 us, 128 blocks
-// 30.3 -> 23.7; 4096 channels int8, 32 blocks 15.8 -> 25.0, 128 blocks
-// 30.5 -> 25.3; sub-bands of 4096 channels, 32 blocks 22.8 -> 27.2, 128
-// blocks 44.3 -> 29.1. At 32 taps the split path's FIR of integer samples is
-// slow (4096 channels int8: 2 blocks 35.9 -> 34.5), and at 1024 channels the
-// lines cross at 8 blocks (complex64, 32 taps 28.3 -> 28.6). Up to 512
-// channels one launch is always faster than two (128 channels, 4 blocks 11.8
-// -> 9.4).
+// sub-bands) of S spectra. A block takes one CU 9 us (128 channels) to 40 us
+// (4096 channels, 32 taps), and a launch of few blocks leaves the other CUs
+// idle, where the FIR and FFT launches spread over more of them. Measured,
+// split / blocked time at 64 and 128 blocks: 2048 channels, 16 taps, complex64
+// 0.90 and 1.25, int8 0.95 and 1.46; 4096 channels, 8 taps 0.97 and 1.23; 1024
+// channels, 32 taps 0.83 and 1.35, 64 taps 0.99 and 1.18. Long windows of wide
+// rows cross later: 4096 channels, 32 taps 0.80 at 128 blocks and 1.35 at 256,
+// 2048 channels 1.03 at 128, 8192 channels, 16 taps 0.84 and 1.38. 512
+// channels, 32 taps 1.04 at 64 blocks; otherwise up to 512 channels one launch
+// is always the faster (256 channels, 32 taps, 16 blocks 15.2 -> 13.7 us, 128
+// channels, 8 taps, 4 blocks 11.8 -> 9.4). Sub-bands of 4096 channels 0.84 at
+// 32 blocks, 1.52 at 128.
 bool block_pays(int dtype, int tp, int log2c, bool pol, int64_t units, int64_t S)
 {
     if (!block_supported(dtype, tp, log2c, pol))
         return false;
     const int64_t rows = block_rows(log2c, pol);
     const int64_t blocks = units * ((S + rows - 1) / rows);
-    if (log2c <= 9)
-        return true;
-    if (!pol && tp >= 32 && (log2c == 10 || dtype == 1 || dtype == 2))
-        return blocks >= 8;
-    return blocks >= (pol ? 64 : 96);
+    int64_t from = 1;
+    if (pol)
+        from = log2c <= 9 ? 1 : tp >= 32 ? 112 : 72;
+    else if (log2c == 9)
+        from = tp == 32 ? 60 : 1;
+    else if (log2c >= 10)
+        from = log2c >= 11 && (tp >= 32 || (log2c == 13 && tp == 16)) ? 160 : 84;
+    return blocks >= from;
 }
 
 hipError_t launch_block(const BlockArgs &a, int dtype, int tp, int log2c, bool pol, hipStream_t st)
