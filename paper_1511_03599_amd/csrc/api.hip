@@ -279,8 +279,8 @@ static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 //          again), spread evenly.
 // Tiles of one height for every size (256 rows forward, 128 adjoint) left
 // most CUs idle below 65536 rows: 1024 channels, 16 taps, complex64, forward
-// 1024 rows 135 -> 12 us, 16384 rows 146 -> 60; adjoint 1024 rows 118 -> 34,
-// 16384 rows 145 -> 119. At 65536 rows and above both rules take about 256
+// 1024 rows 135 -> 9 us, 16384 rows 146 -> 49; adjoint 1024 rows 118 -> 34,
+// 16384 rows 145 -> 114. At 65536 rows and above both rules take about 256
 // rows (16-row tiles: forward 301 us against 210).
 static int tile_rows(int64_t B, int64_t rows, int rb, int64_t fixed, int64_t halo, int slots)
 {

@@ -3,10 +3,10 @@
 // launch per call; large ones run as launches of the fused or blocked forward
 // where those apply (BT_ALONE_SAMPLES), in the same stream.
 //
-// The persistent kernel's work is a table of tiles built on the host when the plan is created. A tile
-// is a run of consecutive filtered spectra of one beam, over all of its
-// channels. A persistent workgroup takes the next tile from an atomic counter
-// and does all of the tile's work itself:
+// The persistent kernel's work is a table of tiles built on the host when the
+// plan is created. A tile is a run of consecutive filtered spectra of one
+// beam, over all of its channels. A persistent workgroup takes the next tile
+// from an atomic counter and does all of the tile's work itself:
 //   1. the register-window FIR of every channel of the tile's rows (wave
 //      tasks of 64*CPT channels x 32 rows spread over the workgroup's waves),
 //      written to the workgroup's own slot of filtered spectra;
@@ -388,7 +388,7 @@ static pfb_status build_batched(int32_t nbeams, const pfb_desc *beams, Batched *
         // or blocked forward, whose filtered spectra stay on the chip; the
         // persistent kernel's go through its slot. The launch's ramp and tail
         // cost some 10 us, what a quarter of the samples at the line take.
-        // (64 uneven beams of 2.1 G samples 12.8 -> 10.9 ms, 6 of 80 M 0.84
+        // (64 uneven beams of 2.1 G samples 12.8 -> 10.8 ms, 6 of 80 M 0.84
         // -> 0.44.)
         // Long windows at 2048 channels and more gain less, on 4 M samples
         // nothing (4096 channels, 32 taps, 10 beams of 4 M 392 -> 447 us;

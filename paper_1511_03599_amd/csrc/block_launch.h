@@ -29,7 +29,7 @@
 // Bound: one workgroup per CU (LDS), two waves per SIMD, so FIR and FFT
 // phases of a CU do not overlap; at 4096 channels, 16 taps and int8 input the
 // VALU issues 64% of the time (86 operations per sample). Measured against
-// FIR + FFT launches (2^27 samples, 16 taps): 4096 channels int8 0.66 -> 0.40
+// FIR + FFT launches (2^27 samples, 16 taps): 4096 channels int8 0.66 -> 0.39
 // ms, complex64 0.78 -> 0.52; 2048 channels complex64 0.79 -> 0.50; 1024
 // channels, 32 taps, 2^26 samples 0.40 -> 0.27; 8 sub-bands of 4096 channels,
 // int8, 2^27 samples 0.92 -> 0.42. With H = 1: 0.49, 0.65, 0.53, 0.29, 0.60.
