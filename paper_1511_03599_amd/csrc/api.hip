@@ -604,13 +604,8 @@ static hipError_t run_fir(const pfb_plan *p, const void *x, const float *h, floa
     a.out_first = s_a;
     a.out_count = n;
     a.y_bstride = y_bstride;
-    if (p->long_fir) {
-        a.SB = 32;
-        a.n_tiles = (int)ceil_div(n, a.SB);
-        a.n_cchunks = (int)ceil_div(d.channels, 64);
-        a.shift = 0;
+    if (p->long_fir)
         return launch_fir_long(a, d.dtype, st);
-    }
     return launch_fir(a, d.dtype, p->tp, p->fir_cpt, false, st, (d.flags & PFB_CONVERT_PER_USE) != 0);
 }
 

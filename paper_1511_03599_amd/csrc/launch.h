@@ -112,7 +112,7 @@ hipError_t launch_fir_cf16(const FirArgs &a, int tp, int cpt, bool per_use, hipS
 hipError_t launch_fir_adjoint(const FirArgs &a, int tp, int cpt, hipStream_t st); // reversed taps, c64
 // FIR for T beyond the register window: tiles of 32 rows (SB = 32), one
 // channel per lane (64 per wave task), no tap padding (shift = 0).
-hipError_t launch_fir_long(const FirArgs &a, int dtype, hipStream_t st);
+hipError_t launch_fir_long(FirArgs a, int dtype, hipStream_t st); // sets its own tiles
 hipError_t launch_gh(const GhArgs &a, int tp, float *gh, hipStream_t st);
 // padded taps tp <= 32; also runs the reduction into gh
 hipError_t launch_gxgh(const GxGhArgs &a, int tp, float *gh, hipStream_t st);

@@ -1,0 +1,27 @@
+"""The long-tap FIR at the edges of its 16-row tiles and 16-tap segments,
+element by element against the FP64 oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1511_03599_amd import synth
+from helpers import c128, say, taps_to_device, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("C,T,S,B,dtype", [
+    (64, 65, 1, 1, "c64"), (65, 80, 15, 2, "ci16"), (63, 81, 16, 1, "ci8"), (128, 96, 17, 3, "cf16"),
+    (1, 79, 33, 1, "c64"), (130, 1024, 5, 1, "ci8"), (96, 112, 1000, 2, "c64"), (77, 95, 31, 1, "cf16")])
+def test_long_taps_tile_and_segment_edges(dev, C, T, S, B, dtype):
+    """Each component is one float32 accumulator over T products, so its error
+    is at most (T + 1) 2^-24 of the sum of the products' magnitudes."""
+    from paper_1511_03599_amd import pfb
+    say(f"long-tap FIR edges C={C} T={T} S={S} B={B} {dtype}")
+    x = synth.noise_stream(B, C, T, S, 2100 + C + T, dtype=dtype).x
+    h = synth.random_taps(C, T, 2101)
+    y = c128(pfb.Plan(C, T, S, B, dtype, pfb.FIR_ONLY).execute(to_device(x, dev), taps_to_device(h, dev)))
+    ref, size = oracle.fir(x, h), oracle.fir(np.abs(x), np.abs(h))
+    bound = (T + 1) * 2.0 ** -24
+    assert np.all(np.abs(y.real - ref.real) <= bound * size.real)
+    assert np.all(np.abs(y.imag - ref.imag) <= bound * size.imag)
