@@ -103,6 +103,7 @@ struct pfb_plan {
     float2 *twiddle = nullptr;   // FFT twiddle table for C
     bool mixed = false;          // C not a power of two: mixed-radix transform
     bool long_fir = false;       // T beyond the register window
+    bool fir_segments = false;   // 33 to 64 taps through the long-tap FIR
     GfftSched gf{};
     float2 *ws_y = nullptr;      // filtered spectra workspace (split path)
     int64_t ws_y_bytes = 0;
@@ -364,6 +365,25 @@ static int split_adjoint_rows(const pfb_desc &d, int tp, int cus)
     return (int)std::max<int64_t>(1, ceil_div((int64_t)rows, u)) * u;
 }
 
+// Whether 33 to 64 taps run faster through the long-tap FIR (16-row tiles,
+// taps rounded up to 16) than through the 64-tap register window (64-row
+// tiles, at most eight waves a CU). In us, for a round of eight 64-row tiles
+// a CU: the window takes whole rounds of 37 (complex64) or 35, the long-tap
+// FIR 38.5 or 31.7 up to 48 taps and 47.7 or 39 above, in proportion, and 6
+// for its first rows. Window -> long-tap, 48 taps: 256 channels, 3000 spectra
+// complex64 33 -> 10 us, int8 41 -> 12; 2048 channels, 9000 spectra 96 -> 85
+// and 97 -> 71; 1024 channels, 65536 spectra 318 (362) and 257 -> 227; 64 taps
+// 31 -> 13, 38 -> 14; 98 (102), 99 -> 85; 301 (407), 255 (278).
+static bool fir_segments_pay(const pfb_desc &d, int cus)
+{
+    if (d.taps <= 32 || d.taps > PFB_MAX_TAPS_WINDOW || (d.flags & (PFB_PLAIN | PFB_CONVERT_PER_USE)))
+        return false;
+    const bool c64 = d.dtype == PFB_C64;
+    const double rounds = (double)d.batch * (double)ceil_div(d.channels, 64) * (double)ceil_div(d.spectra, 64) / (8.0 * cus);
+    const double per_round = d.taps <= 48 ? (c64 ? 38.5 : 31.7) : (c64 ? 47.7 : 39.0);
+    return 6.0 + per_round * rounds < 0.97 * (c64 ? 37.0 : 35.0) * std::ceil(rounds);
+}
+
 static int64_t row_bytes_in(const pfb_desc &d) { return (int64_t)d.channels * bytes_per_sample(d.dtype); }
 
 // The blocked kernel addresses a block's raw rows, and its spectra, through
@@ -423,6 +443,7 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
     const double waves_per_row = (double)d->batch * (double)ceil_div(d->channels, 64 * p->fir_cpt);
     if (!tuned && p->tp <= 32 && waves_per_row * (double)ceil_div(d->spectra, p->fir_sb) < 8.0 * p->num_cus)
         p->fir_sb = p->tp <= 16 ? 16 : 32;
+    p->fir_segments = !tuned && fir_segments_pay(*d, p->num_cus);
     if (tuned) {
         if (te.fir_cpt == 1 || (te.fir_cpt == 2 && cpt2_ok))
             p->fir_cpt = te.fir_cpt;
@@ -604,8 +625,11 @@ static hipError_t run_fir(const pfb_plan *p, const void *x, const float *h, floa
     a.out_first = s_a;
     a.out_count = n;
     a.y_bstride = y_bstride;
-    if (p->long_fir)
+    if (p->long_fir || p->fir_segments) {
+        // up to 64 taps the padding leads, as in the register window
+        a.shift = p->long_fir ? 0 : (16 - d.taps % 16) % 16;
         return launch_fir_long(a, d.dtype, st);
+    }
     return launch_fir(a, d.dtype, p->tp, p->fir_cpt, false, st, (d.flags & PFB_CONVERT_PER_USE) != 0);
 }
 

@@ -1,5 +1,6 @@
-// Polyphase FIR for tap counts beyond the register window (T > 64): the FIR
-// of Algorithm 1, y[s][c] = sum_{t<T} h[t][c] x[s+t][c].
+// Polyphase FIR for tap counts beyond the register window (T > 64), and for
+// 33 to 64 taps where it is the faster one (fir_segments_pay in api.hip): the
+// FIR of Algorithm 1, y[s][c] = sum_{t<T} h[t][c] x[s+t][c].
 //
 // One wave owns 64 adjacent channels (one per lane) of a tile of N = 16
 // filtered spectra and keeps the tile's N complex sums in registers. It walks
@@ -8,8 +9,8 @@
 // that a segment starts with are those that the one before ended on, so a
 // tile reads each of its N + T - 1 raw rows once. Each sum takes its taps in
 // ascending order from one accumulator, so the result is the sequential sum a
-// single window of T taps would give (the last segment's zero taps add exact
-// zeros). Rows are shared by T / N tiles; the caches serve the re-reads.
+// single window of T taps would give (zero taps that fill a segment, a.shift
+// of them in front, the others behind, add exact zeros). Rows are shared by T / N tiles; the caches serve the re-reads.
 //
 // Rows, taps and stores go through bounded views of one row's 64 channels,
 // empty outside the stream, the filter or the tile: every load is
@@ -55,22 +56,24 @@ template <int DT> __global__ __launch_bounds__(256, 3) void fir_long_kernel(FirA
     const int64_t left_out = a.out_first + a.out_count - s_begin;
     const int nout = (int)(left_out < N ? left_out : N);
 
-    // the next raw row and tap row to load, and how many there are
+    // the next raw row and tap row to load, and how many there are; a.shift
+    // zero taps come first, `lead` of the rows lie before the stream
     const int64_t row_bytes = (int64_t)a.C * SB, tap_bytes = (int64_t)a.C * 4;
     const char *xp = reinterpret_cast<const char *>(a.x) +
-                     ((int64_t)b * a.in_bstride + s_begin * a.C + (int64_t)cch * 64) * SB;
-    const char *hp_next = reinterpret_cast<const char *>(a.h) + (int64_t)cch * 64 * 4;
-    const int64_t left_in = a.in_rows - s_begin;
+                     ((int64_t)b * a.in_bstride + (s_begin - a.shift) * a.C + (int64_t)cch * 64) * SB;
+    const char *hp_next = reinterpret_cast<const char *>(a.h) + (int64_t)cch * 64 * 4 - a.shift * tap_bytes;
+    const int64_t left_in = a.in_rows - s_begin + a.shift;
     int rows_left = (int)(left_in < 0x40000000 ? left_in : 0x40000000);
-    int taps_left = a.T;
+    int lead = s_begin < a.shift ? a.shift - (int)s_begin : 0, taps_left = a.T + a.shift;
     auto ld = [&](Packed<DT, 1> &o) PFB_INLINE {
-        buf_load_packed<DT, 1>(buf_view(xp, rows_left > 0 ? cw * SB : 0), lane * SB, o);
+        buf_load_packed<DT, 1>(buf_view(xp, lead <= 0 && rows_left > 0 ? cw * SB : 0), lane * SB, o);
         xp += row_bytes;
         --rows_left;
+        --lead;
     };
     auto ld_tap = [&](float &o) PFB_INLINE {
         Packed<DT_CI16, 1> t; // 4 bytes
-        buf_load_packed<DT_CI16, 1>(buf_view(hp_next, taps_left > 0 ? cw * 4 : 0), lane * 4, t);
+        buf_load_packed<DT_CI16, 1>(buf_view(hp_next, taps_left > 0 && taps_left <= a.T ? cw * 4 : 0), lane * 4, t);
         o = __uint_as_float(t.w[0]);
         hp_next += tap_bytes;
         --taps_left;
@@ -89,7 +92,7 @@ template <int DT> __global__ __launch_bounds__(256, 3) void fir_long_kernel(FirA
         sfor<N - 1>([&](auto j) PFB_INLINE { unpack<DT, 1>(first[j], w[j]); });
     }
 #pragma unroll 1
-    for (int g = (a.T + N - 1) / N; g > 0; --g) {
+    for (int g = (a.T + a.shift + N - 1) / N; g > 0; --g) {
         // sum o reads window rows o + j, j < N, of which row o + N - 1 is new
         sfor<N>([&](auto oc) PFB_INLINE {
             constexpr int o = decltype(oc)::value;

@@ -1,5 +1,6 @@
-"""The long-tap FIR at the edges of its 16-row tiles and 16-tap segments,
-element by element against the FP64 oracle."""
+"""The long-tap FIR at the edges of its 16-row tiles and 16-tap segments:
+element by element against the FP64 oracle, and up to 64 taps bit for bit
+against the register window."""
 import numpy as np
 import pytest
 
@@ -25,3 +26,18 @@ def test_long_taps_tile_and_segment_edges(dev, C, T, S, B, dtype):
     bound = (T + 1) * 2.0 ** -24
     assert np.all(np.abs(y.real - ref.real) <= bound * size.real)
     assert np.all(np.abs(y.imag - ref.imag) <= bound * size.imag)
+
+
+@pytest.mark.parametrize("C,T,S,B", [(64, 33, 1, 1), (63, 48, 16, 2), (65, 49, 17, 1), (256, 64, 3000, 1),
+                                     (1000, 40, 700, 3), (1, 63, 100, 1)])
+@pytest.mark.parametrize("dtype", ["c64", "ci16", "ci8", "cf16"])
+def test_33_to_64_taps_equal_the_register_window(dev, C, T, S, B, dtype):
+    """Small launches of 33 to 64 taps go through the long-tap FIR; a plain
+    plan keeps the register window. Same sums in the same order: same bits."""
+    import torch
+    from paper_1511_03599_amd import pfb
+    say(f"33 to 64 taps C={C} T={T} S={S} B={B} {dtype}")
+    x = synth.device_quantised_noise((B, S + T - 1, C), dtype, 2200 + C + T, dev)
+    h = taps_to_device(synth.random_taps(C, T, 2201), dev)
+    y = pfb.Plan(C, T, S, B, dtype, pfb.FIR_ONLY).execute(x, h)
+    assert torch.equal(y, pfb.Plan(C, T, S, B, dtype, pfb.FIR_ONLY | pfb.PLAIN).execute(x, h))
