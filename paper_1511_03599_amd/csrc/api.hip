@@ -369,7 +369,7 @@ static int split_adjoint_rows(const pfb_desc &d, int tp, int cus)
 // taps rounded up to 16) than through the 64-tap register window (64-row
 // tiles, at most eight waves a CU). In us, for a round of eight 64-row tiles
 // a CU: the window takes whole rounds of 37 (complex64) or 35, the long-tap
-// FIR 38.5 or 31.7 up to 48 taps and 47.7 or 39 above, in proportion, and 6
+// FIR 38.5 or 31.7 up to 48 taps and 50 or 39 above, in proportion, and 6
 // for its first rows. Window -> long-tap, 48 taps: 256 channels, 3000 spectra
 // complex64 33 -> 10 us, int8 41 -> 12; 2048 channels, 9000 spectra 96 -> 85
 // and 97 -> 71; 1024 channels, 65536 spectra 318 (362) and 257 -> 227; 64 taps
@@ -380,7 +380,7 @@ static bool fir_segments_pay(const pfb_desc &d, int cus)
         return false;
     const bool c64 = d.dtype == PFB_C64;
     const double rounds = (double)d.batch * (double)ceil_div(d.channels, 64) * (double)ceil_div(d.spectra, 64) / (8.0 * cus);
-    const double per_round = d.taps <= 48 ? (c64 ? 38.5 : 31.7) : (c64 ? 47.7 : 39.0);
+    const double per_round = d.taps <= 48 ? (c64 ? 38.5 : 31.7) : (c64 ? 50.0 : 39.0);
     return 6.0 + per_round * rounds < 0.97 * (c64 ? 37.0 : 35.0) * std::ceil(rounds);
 }
 

@@ -38,10 +38,10 @@ int block_rows(int log2c, bool pol)
 // idle, where the FIR and FFT launches spread over more of them. Measured,
 // split / blocked time at 64 and 128 blocks: 2048 channels, 16 taps, complex64
 // 0.90 and 1.25, int8 0.95 and 1.46; 4096 channels, 8 taps 0.97 and 1.23; 1024
-// channels, 32 taps 0.83 and 1.35, 64 taps complex64 1.00 and 1.17, int8 0.99 and
-// 0.93 (1.44 at 256). Long windows of wide
-// rows cross later: 4096 channels, 32 taps 0.80 at 128 blocks and 1.35 at 256,
-// 2048 channels 1.03 at 128, 8192 channels, 16 taps 0.84 and 1.38. 512
+// channels, 32 taps 0.83 and 1.35, 64 taps complex64 1.00 and 1.17, int8 0.99
+// and 0.93 (1.44 at 256). Long windows of wide rows cross later: 4096 channels,
+// 32 taps 0.80 at 128 blocks and 1.35 at 256, 2048 channels 1.03 at 128, 8192
+// channels, 16 taps 0.84 and 1.38. 512
 // channels, 32 taps 1.04 at 64 blocks; otherwise up to 512 channels one launch
 // is always the faster (256 channels, 32 taps, 16 blocks 15.2 -> 13.7 us, 128
 // channels, 8 taps, 4 blocks 11.8 -> 9.4), but for 33 to 64 taps, where the

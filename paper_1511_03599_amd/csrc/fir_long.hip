@@ -34,7 +34,9 @@ namespace pfb {
 constexpr int FIR_LONG_ROWS = 16;      // sums and window rows per lane, taps per segment
 constexpr unsigned FIR_LONG_GRID = 1 << 20; // workgroups along x (a dimension holds under 2^32 threads)
 
-template <int DT> __global__ __launch_bounds__(256, 3) void fir_long_kernel(FirArgs a)
+// LEAD: a.shift zero taps come first (the counters that keep them and the rows
+// before the stream out cost long filters 5 to 10%).
+template <int DT, bool LEAD> __global__ __launch_bounds__(256, 3) void fir_long_kernel(FirArgs a)
 {
     constexpr int N = FIR_LONG_ROWS;
     constexpr int D = 4; // rows in flight ahead of the window
@@ -56,24 +58,25 @@ template <int DT> __global__ __launch_bounds__(256, 3) void fir_long_kernel(FirA
     const int64_t left_out = a.out_first + a.out_count - s_begin;
     const int nout = (int)(left_out < N ? left_out : N);
 
-    // the next raw row and tap row to load, and how many there are; a.shift
-    // zero taps come first, `lead` of the rows lie before the stream
+    // the next raw row and tap row to load, and how many there are; `lead`
+    // of the rows lie before the stream
+    const int shift = LEAD ? a.shift : 0;
     const int64_t row_bytes = (int64_t)a.C * SB, tap_bytes = (int64_t)a.C * 4;
     const char *xp = reinterpret_cast<const char *>(a.x) +
-                     ((int64_t)b * a.in_bstride + (s_begin - a.shift) * a.C + (int64_t)cch * 64) * SB;
-    const char *hp_next = reinterpret_cast<const char *>(a.h) + (int64_t)cch * 64 * 4 - a.shift * tap_bytes;
-    const int64_t left_in = a.in_rows - s_begin + a.shift;
+                     ((int64_t)b * a.in_bstride + (s_begin - shift) * a.C + (int64_t)cch * 64) * SB;
+    const char *hp_next = reinterpret_cast<const char *>(a.h) + (int64_t)cch * 64 * 4 - shift * tap_bytes;
+    const int64_t left_in = a.in_rows - s_begin + shift;
     int rows_left = (int)(left_in < 0x40000000 ? left_in : 0x40000000);
-    int lead = s_begin < a.shift ? a.shift - (int)s_begin : 0, taps_left = a.T + a.shift;
+    int lead = s_begin < shift ? shift - (int)s_begin : 0, taps_left = a.T + shift;
     auto ld = [&](Packed<DT, 1> &o) PFB_INLINE {
-        buf_load_packed<DT, 1>(buf_view(xp, lead <= 0 && rows_left > 0 ? cw * SB : 0), lane * SB, o);
+        buf_load_packed<DT, 1>(buf_view(xp, (!LEAD || lead <= 0) && rows_left > 0 ? cw * SB : 0), lane * SB, o);
         xp += row_bytes;
         --rows_left;
         --lead;
     };
     auto ld_tap = [&](float &o) PFB_INLINE {
         Packed<DT_CI16, 1> t; // 4 bytes
-        buf_load_packed<DT_CI16, 1>(buf_view(hp_next, taps_left > 0 && taps_left <= a.T ? cw * 4 : 0), lane * 4, t);
+        buf_load_packed<DT_CI16, 1>(buf_view(hp_next, taps_left > 0 && (!LEAD || taps_left <= a.T) ? cw * 4 : 0), lane * 4, t);
         o = __uint_as_float(t.w[0]);
         hp_next += tap_bytes;
         --taps_left;
@@ -92,7 +95,7 @@ template <int DT> __global__ __launch_bounds__(256, 3) void fir_long_kernel(FirA
         sfor<N - 1>([&](auto j) PFB_INLINE { unpack<DT, 1>(first[j], w[j]); });
     }
 #pragma unroll 1
-    for (int g = (a.T + a.shift + N - 1) / N; g > 0; --g) {
+    for (int g = (a.T + shift + N - 1) / N; g > 0; --g) {
         // sum o reads window rows o + j, j < N, of which row o + N - 1 is new
         sfor<N>([&](auto oc) PFB_INLINE {
             constexpr int o = decltype(oc)::value;
@@ -122,11 +125,8 @@ template <int DT> __global__ __launch_bounds__(256, 3) void fir_long_kernel(FirA
     });
 }
 
-hipError_t launch_fir_long(FirArgs a, int dtype, hipStream_t st)
+template <bool LEAD> static hipError_t launch_fir_long_lead(const FirArgs &a, int dtype, hipStream_t st)
 {
-    a.SB = FIR_LONG_ROWS;
-    a.n_tiles = (int)((a.out_count + FIR_LONG_ROWS - 1) / FIR_LONG_ROWS);
-    a.n_cchunks = (int)(((int64_t)a.C + 63) / 64);
     const int64_t waves = (int64_t)a.B * a.n_tiles * a.n_cchunks;
     const int64_t blocks = (waves + 3) / 4;
     if (blocks <= 0)
@@ -134,13 +134,21 @@ hipError_t launch_fir_long(FirArgs a, int dtype, hipStream_t st)
     const unsigned gx = (unsigned)(blocks < FIR_LONG_GRID ? blocks : FIR_LONG_GRID);
     const dim3 grid(gx, (unsigned)((blocks + gx - 1) / gx)), block(256);
     switch (dtype) {
-    case DT_C64: hipLaunchKernelGGL(fir_long_kernel<DT_C64>, grid, block, 0, st, a); break;
-    case DT_CI16: hipLaunchKernelGGL(fir_long_kernel<DT_CI16>, grid, block, 0, st, a); break;
-    case DT_CI8: hipLaunchKernelGGL(fir_long_kernel<DT_CI8>, grid, block, 0, st, a); break;
-    case DT_CF16: hipLaunchKernelGGL(fir_long_kernel<DT_CF16>, grid, block, 0, st, a); break;
+    case DT_C64: hipLaunchKernelGGL((fir_long_kernel<DT_C64, LEAD>), grid, block, 0, st, a); break;
+    case DT_CI16: hipLaunchKernelGGL((fir_long_kernel<DT_CI16, LEAD>), grid, block, 0, st, a); break;
+    case DT_CI8: hipLaunchKernelGGL((fir_long_kernel<DT_CI8, LEAD>), grid, block, 0, st, a); break;
+    case DT_CF16: hipLaunchKernelGGL((fir_long_kernel<DT_CF16, LEAD>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t launch_fir_long(FirArgs a, int dtype, hipStream_t st)
+{
+    a.SB = FIR_LONG_ROWS;
+    a.n_tiles = (int)((a.out_count + FIR_LONG_ROWS - 1) / FIR_LONG_ROWS);
+    a.n_cchunks = (int)(((int64_t)a.C + 63) / 64);
+    return a.shift > 0 ? launch_fir_long_lead<true>(a, dtype, st) : launch_fir_long_lead<false>(a, dtype, st);
 }
 
 } // namespace pfb
