@@ -24,9 +24,23 @@
 // A group of G lanes owns one row: as many as the pass with the most
 // butterflies per gf_butterflies(R) asks for, rounded to a power of two up to
 // a wave (several rows per block of 256 lanes), to whole waves above (one row
-// per block). Groups of fewer than 16 lanes write less than a line at a time
-// and store through L2 (96 channels, 2^20 spectra: non-temporal 935 us, plain
-// 389; from 16 lanes on non-temporal is the faster, 240 channels 286 to 303).
+// per block).
+//
+// Stores and lines. A group that writes less than a 128-byte line at a time
+// stores through L2, which gathers the lines: groups of fewer than 16 lanes
+// (96 channels, 2^20 spectra: non-temporal 935 us, plain 389; from 16 lanes on
+// non-temporal is the faster, 240 channels 286 to 303). So does a group of 16
+// whose rows start off the 64-byte sectors and whose last pass gives a lane
+// several butterflies: the pieces of a line are then written a butterfly
+// apart. T = 1, 2^26 samples, FIR and transform, with a wave per row and one
+// radix per factor, with non-temporal stores, and now: 175 channels 616, 806,
+// 547 us; 147 660, 779, 561; 125 698, 780, 548; 162 610, 665, 502. (200
+// channels, on the sectors, 520, 424 and 448 with plain stores; 168, one
+// butterfly a lane, 548, 432 and 463.)
+// Rows off the lines gain from one sweep per pass too: groups of 32 take a
+// wave where every pass then has work for most lanes (343 channels 498, 582,
+// 504; 294 544, 526, 490; 250, whose first pass would use 25 lanes, 529, 506,
+// 528 with a wave).
 #include <algorithm>
 
 #include "fft_device.h"
@@ -156,8 +170,8 @@ template <class T> __device__ __forceinline__ T &gf_at(T *base, uint32_t idx)
 
 // One pass of radix R over the row; MULTI: the group spans several waves.
 template <int R, bool FIRST, bool LAST, bool INV, bool MULTI>
-__device__ __forceinline__ void gf_pass(const GfftPass ps, int C, int G, int lane, const float2 *in, float2 *out,
-                                        float2 *row, const float2 *tw)
+__device__ __forceinline__ void gf_pass(const GfftPass ps, int C, int G, bool nt, int lane, const float2 *in,
+                                        float2 *out, float2 *row, const float2 *tw)
 {
     constexpr int NB = gf_butterflies(R); // C/R <= NB * G
     const int CR = C / R, L = ps.stride;
@@ -185,9 +199,9 @@ __device__ __forceinline__ void gf_pass(const GfftPass ps, int C, int G, int lan
                 sfor<R>([&](auto i) PFB_INLINE {
                     float2 *d = &gf_at(out, (uint32_t)(j + decltype(i)::value * CR));
                     const float2 z = INV ? conj2(v[q][i]) : v[q][i];
-                    if (MULTI || G >= 16)
+                    if (MULTI || nt)
                         store_nt(d, z);
-                    else // less than a line at a time: L2 gathers it
+                    else // less than a line at a time
                         *d = z;
                 });
         }
@@ -206,11 +220,11 @@ __device__ __forceinline__ void gf_pass(const GfftPass ps, int C, int G, int lan
 }
 
 template <bool FIRST, bool LAST, bool INV, bool MULTI>
-__device__ __forceinline__ void gf_pass_any(const GfftPass ps, int C, int G, int lane, const float2 *in, float2 *out,
-                                            float2 *row, const float2 *tw)
+__device__ __forceinline__ void gf_pass_any(const GfftPass ps, int C, int G, bool nt, int lane, const float2 *in,
+                                            float2 *out, float2 *row, const float2 *tw)
 {
 #define PFB_GF(R)                                                                                            \
-    case R: gf_pass<R, FIRST, LAST, INV, MULTI>(ps, C, G, lane, in, out, row, tw); break;
+    case R: gf_pass<R, FIRST, LAST, INV, MULTI>(ps, C, G, nt, lane, in, out, row, tw); break;
     switch (ps.radix) {
         PFB_GF(16)
         PFB_GF(15)
@@ -224,7 +238,7 @@ __device__ __forceinline__ void gf_pass_any(const GfftPass ps, int C, int G, int
         PFB_GF(4)
         PFB_GF(3)
     default:
-        gf_pass<2, FIRST, LAST, INV, MULTI>(ps, C, G, lane, in, out, row, tw);
+        gf_pass<2, FIRST, LAST, INV, MULTI>(ps, C, G, nt, lane, in, out, row, tw);
     }
 #undef PFB_GF
 }
@@ -247,14 +261,14 @@ __global__ __launch_bounds__(MAXT) void gfft_kernel(FftArgs a, GfftSched s)
     const float2 *in = a.in + g * a.in_gstride + r * C;
     float2 *out = a.out + g * a.out_gstride + r * C;
     float2 *row = gf_lds + grp * (C + C / 16 + 1);
-    gf_pass_any<true, false, INV, MULTI>(s.pass[0], C, G, lane, in, out, row, a.tw);
+    gf_pass_any<true, false, INV, MULTI>(s.pass[0], C, G, s.nt, lane, in, out, row, a.tw);
     for (int p = 1; p + 1 < s.npass; ++p) {
         // opaque: every radix's addresses would be hoisted out of the loop
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        gf_pass_any<false, false, INV, MULTI>(s.pass[p], C, G, ln, in, out, row, a.tw);
+        gf_pass_any<false, false, INV, MULTI>(s.pass[p], C, G, s.nt, ln, in, out, row, a.tw);
     }
-    gf_pass_any<false, true, INV, MULTI>(s.pass[s.npass - 1], C, G, lane, in, out, row, a.tw);
+    gf_pass_any<false, true, INV, MULTI>(s.pass[s.npass - 1], C, G, s.nt, lane, in, out, row, a.tw);
 }
 
 // The fewest radices whose product is `rem`, none above `most`; of those the
@@ -307,6 +321,9 @@ bool gfft_schedule(int C, GfftSched *s)
         const int per = radix[p] * gf_butterflies(radix[p]);
         lanes = std::max(lanes, (C + per - 1) / per);
     }
+    const int first = C / radix[0], last = C / radix[np - 1]; // butterflies of the largest and the smallest radix
+    if (C % 16 != 0 && lanes > 16 && lanes <= 32 && first <= 64 && first >= (C % 8 != 0 ? 35 : 48))
+        lanes = 64;
     if (lanes <= 64) {
         t.group = 1;
         while (t.group < lanes)
@@ -316,6 +333,7 @@ bool gfft_schedule(int C, GfftSched *s)
         t.group = (lanes + 63) / 64 * 64;
         t.rows_per_block = 1;
     }
+    t.nt = t.group > 16 || (t.group == 16 && (C % 8 == 0 || last <= 16));
     *s = t;
     return true;
 }

@@ -138,6 +138,7 @@ struct GfftSched {
     int npass;
     int group;           // lanes per row
     int rows_per_block;
+    bool nt;             // the last pass stores past L2
     int tw_entries;
     GfftPass pass[GF_MAX_PASS];
 };

@@ -85,3 +85,10 @@ def test_mixed_radix_schedules(dev, C, S):
     gx_r, gh_r = oracle.pfb_adjoint(x, h, gY)
     assert rel_l2(c128(gx), gx_r) <= GX_TOL
     assert rel_l2(gh.cpu().numpy().astype(np.float64), gh_r) <= GH_TOL
+
+
+# rows off the sectors: 16-lane groups that store through L2, groups widened
+# to a wave; row counts that leave a block part empty
+@pytest.mark.parametrize("C,S", [(125, 33), (147, 15), (175, 17), (252, 5), (343, 9), (441, 6)])
+def test_mixed_radix_rows_off_the_lines(dev, C, S):
+    test_mixed_radix_schedules(dev, C, S)

@@ -1,0 +1,44 @@
+"""The rules that choose kernels, tiles and workspaces, called in the built
+library on the host (no device)."""
+import ctypes
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def L():
+    from paper_1511_03599_amd import pfb
+    if not os.path.exists(pfb.LIB_PATH):
+        pytest.skip("libpfb.so not built")
+    return pfb.lib()
+
+
+class GfftPass(ctypes.Structure):
+    _fields_ = [("radix", ctypes.c_int), ("stride", ctypes.c_int), ("magic", ctypes.c_uint32), ("tw", ctypes.c_int)]
+
+
+class GfftSched(ctypes.Structure):
+    _fields_ = [("C", ctypes.c_int), ("npass", ctypes.c_int), ("group", ctypes.c_int),
+                ("rows_per_block", ctypes.c_int), ("nt", ctypes.c_bool), ("tw_entries", ctypes.c_int),
+                ("passes", GfftPass * 8)]
+
+
+def test_mixed_radix_groups_write_whole_lines(L):
+    """Groups of up to 16 lanes store past L2 only where rows start on sectors or
+    the last pass is one step; rows off them have no group of 32 lanes where a
+    wave is filled."""
+    schedule = L._ZN3pfb13gfft_scheduleEiPNS_9GfftSchedE
+    schedule.restype = ctypes.c_bool
+    s = GfftSched()
+    for C in range(33, 8192):
+        if C & (C - 1) == 0 or not schedule(C, ctypes.byref(s)):
+            continue
+        assert s.group * s.rows_per_block == 256 or (s.group % 64 == 0 and s.rows_per_block == 1), C
+        radix = [s.passes[p].radix for p in range(s.npass)]
+        assert all(C // r <= s.group * (1 if r > 8 else 16 // r) for r in radix), C
+        first, last = C // radix[0], C // radix[-1]
+        if s.group <= 16:
+            assert s.nt == (s.group == 16 and (C % 8 == 0 or last <= 16)), C
+        else:
+            assert s.nt and not (s.group == 32 and C % 8 and 35 <= first <= 64), C
