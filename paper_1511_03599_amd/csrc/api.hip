@@ -111,7 +111,8 @@ struct pfb_plan {
     int64_t ws_gy_bytes = 0;
     float *ws_gh = nullptr;      // backward: tap-gradient partials
     int64_t ws_gh_bytes = 0;
-    int gh_sb = 256;
+    int gh_sb = 256;             // raw spectra per tile of the combined gradients
+    int gh_only_sb = 256;        // filtered spectra per tile of the tap gradient alone
     bool bwd_fused = false;      // fused adjoint kernel
     bool bwd_ws = false;         // ... its wave-specialised form
     int bwd_sb = 256;            // gx rows per fused adjoint tile
@@ -365,6 +366,40 @@ static int split_adjoint_rows(const pfb_desc &d, int tp, int cus)
     return (int)std::max<int64_t>(1, ceil_div((int64_t)rows, u)) * u;
 }
 
+// Filtered spectra per wave tile of the tap gradient alone (gh_partial_kernel).
+// Where that has a branch-free form (up to 32 taps, whole channel chunks) the
+// least of, in us: the stream's bytes with the rows that a tile reads again at
+// 4.5 TB/s; 0.25 for every row of the tile that ends the stream and so tests
+// each of its rows; 0.011 for a partial in the reduction, whose waves add them
+// one after the other; and 0.04 for a row of a tile, the start and end of the
+// launch. Fitted to nine heights each at 39 shapes, whose best it misses by up
+// to 4%. 256 rows at every size -> the heights of the combined pass -> these:
+// 64 channels x 65536 spectra, 8 taps 49 -> 73 -> 36 us; 128 x 65000, 16 taps
+// 138 -> 75 -> 59; 1024 x 16384, 32 taps 108 -> 125 -> 108; 1024 x 16500, 24
+// taps 171 -> 157 -> 125; 4096 x 8192 x 2, 16 taps 419 -> 407 -> 420. The
+// tested forms want the many waves of split_adjoint_rows.
+static int tap_gradient_rows(const pfb_desc &d, int tp, int cus)
+{
+    if (tp > 32 || d.channels % 64 != 0)
+        return split_adjoint_rows(d, tp, cus);
+    const int u = tp > 16 ? tp : 16;
+    const double B = (double)d.batch, S = (double)d.spectra;
+    const double bytes_us = 16.0 * B * S * (double)d.channels / (4.5e6 * cus / 256.0);
+    int best = u;
+    double best_us = 0.0;
+    for (int sb = u; sb <= 256; sb += u) {
+        const int64_t tiles = ceil_div(d.spectra, sb);
+        const int64_t clean = std::min(tiles, std::max<int64_t>(0, d.spectra + d.taps - tp) / sb);
+        const int64_t tested = clean == tiles ? 0 : clean < tiles - 1 ? sb : d.spectra - (tiles - 1) * sb;
+        const double us = bytes_us * (1.0 + 0.75 * (tp - 1) / sb) + 0.25 * (double)tested + 0.011 * B * (double)tiles + 0.04 * sb;
+        if (sb == u || us < best_us) {
+            best_us = us;
+            best = sb;
+        }
+    }
+    return best;
+}
+
 // Whether 33 to 64 taps run faster through the long-tap FIR (16-row tiles,
 // taps rounded up to 16) than through the 64-tap register window (64-row
 // tiles, at most eight waves a CU). In us, for a round of eight 64-row tiles
@@ -539,9 +574,11 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
                 if (st != PFB_OK)
                     return st;
                 p->gh_sb = split_adjoint_rows(*d, p->tp, p->num_cus);
-                // tiles of gh_sb filtered spectra (gh_partial_kernel) or of
-                // gh_sb raw spectra (gxgh_kernel), whichever is more
-                parts = (int64_t)d->batch * ceil_div(d->spectra + d->taps - 1, p->gh_sb);
+                p->gh_only_sb = tap_gradient_rows(*d, p->tp, p->num_cus);
+                // tiles of gh_only_sb filtered spectra (gh_partial_kernel) or
+                // of gh_sb raw spectra (gxgh_kernel), whichever are more
+                parts = (int64_t)d->batch * std::max(ceil_div(d->spectra, p->gh_only_sb),
+                                                     ceil_div(d->spectra + d->taps - 1, p->gh_sb));
             }
             p->ws_gh_bytes = parts * d->taps * d->channels * 4;
             st = dev_alloc(reinterpret_cast<void **>(&p->ws_gh), p->ws_gh_bytes, "tap-gradient partials");
@@ -983,7 +1020,7 @@ extern "C" pfb_status pfb_backward(pfb_plan *p, const void *x, const float *taps
         a.C = d.channels;
         a.T = d.taps;
         a.B = d.batch;
-        a.SB = p->gh_sb;
+        a.SB = p->gh_only_sb;
         a.n_tiles = (int)ceil_div(S, a.SB);
         a.n_cchunks = (int)ceil_div(C, 64);
         a.S = S;

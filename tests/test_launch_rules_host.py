@@ -5,6 +5,8 @@ import os
 
 import pytest
 
+from hostlib import host_run
+
 
 @pytest.fixture(scope="module")
 def L():
@@ -42,3 +44,19 @@ def test_mixed_radix_groups_write_whole_lines(L):
             assert s.nt == (s.group == 16 and (C % 8 == 0 or last <= 16)), C
         else:
             assert s.nt and not (s.group == 32 and C % 8 and 35 <= first <= 64), C
+
+
+@pytest.mark.parametrize("C,T,S,B,rows", [
+    # tiles as high as at every size before, or fewer partials: never many
+    # more of them than the reduction adds in the time the stream is read in
+    (64, 8, 65536, 1, 64), (64, 4, 10000, 4, 64), (128, 16, 65536, 1, 96), (1024, 32, 16384, 1, 192), (1000, 16, 10000, 1, 16)])
+def test_tiles_of_the_tap_gradient_alone(tmp_path_factory, C, T, S, B, rows):
+    got = host_run(tmp_path_factory, f"""
+p = plan({C}, {T}, {S}, {B})
+events()
+assert L.pfb_backward(p, A, A, A, None, A, None) == 0
+result = [e for e in events() if "gh_partial" in e[0]]
+""")
+    assert len(got) >= 1
+    waves = B * -(-C // 64) * -(-S // rows)
+    assert sum(n for _, n in got) <= -(-waves // 4) + len(got)
