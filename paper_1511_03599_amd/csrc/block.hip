@@ -35,22 +35,34 @@ int block_rows(int log2c, bool pol)
 // Whether the blocked kernel is the faster one for `units` streams (or
 // sub-bands) of S spectra. A block takes one CU 9 us (128 channels) to 40 us
 // (4096 channels, 32 taps), and a launch of few blocks leaves the other CUs
-// idle, where the FIR and FFT launches spread over more of them. Measured,
-// split / blocked time at 64 and 128 blocks: 2048 channels, 16 taps, complex64
-// 0.90 and 1.25, int8 0.95 and 1.46; 4096 channels, 8 taps 0.97 and 1.23; 1024
-// channels, 32 taps 0.83 and 1.35, 64 taps complex64 1.00 and 1.17, int8 0.99
-// and 0.93 (1.44 at 256). Long windows of wide rows cross later: 4096 channels,
-// 32 taps 0.80 at 128 blocks and 1.35 at 256, 2048 channels 1.03 at 128, 8192
-// channels, 16 taps 0.84 and 1.38. 512
-// channels, 32 taps 1.04 at 64 blocks; otherwise up to 512 channels one launch
-// is always the faster (256 channels, 32 taps, 16 blocks 15.2 -> 13.7 us, 128
-// channels, 8 taps, 4 blocks 11.8 -> 9.4), but for 33 to 64 taps, where the
-// long-tap FIR serves small launches: 256 channels, 64 taps 0.90 and 1.17, 40
-// taps int8 0.72 and 0.88 (1.40 at 256). Sub-bands of 4096 channels 0.84 at
-// 32 blocks, 1.52 at 128.
+// idle, where the FIR and FFT launches spread over more of them. Split over
+// blocked time, on 256 CUs, at 64 and 128 blocks and where noted 32 or 256;
+// a line between two measured counts is where the time interpolates to equal:
+//   2048 channels, 16 taps        complex64 0.90, 1.25; int8 0.95, 1.46
+//   4096 channels, 8 taps         0.97, 1.23
+//   1024 channels, 32 taps        0.83, 1.35
+//   1024 channels, 64 taps        complex64 1.00, 1.17; int8 0.99, 0.93 (256: 1.44)
+//   4096 channels, 32 taps        128: 0.80; 256: 1.35
+//   2048 channels, 32 taps        128: 1.03
+//   8192 channels, 16 taps        0.84 and 1.38
+//   512 channels, 32 taps         64: 1.04
+//   256 channels, 64 taps         0.90, 1.17; 40 taps int8 0.72, 0.88 (256: 1.40)
+//   sub-bands of 4096 channels    32: 0.84; 128: 1.52
+// Otherwise up to 512 channels one launch is the faster from one block on
+// (256 channels, 32 taps, 16 blocks 15.2 -> 13.7 us, 128 channels, 8 taps, 4
+// blocks 11.8 -> 9.4), but for part of a block at 17 to 32 taps, which still
+// takes the time of a whole one. Split and blocked, in us: 128 channels
+// complex64 1 spectrum 8.5, 13.9, 20 spectra 12.8, 14.0, 64 spectra 13.0,
+// 14.0; int8 5 spectra 10.7, 14.2, 20 spectra 15.7, 14.2 (its FIR tests the
+// rows of a ragged tile); 256 channels 5 spectra 9.5, 12.9, 16 spectra 13.3,
+// 12.9; 32 channels 32 spectra 15.7, 12.2. (With FIR tiles of 128 rows the
+// split path took 12.2 at 1 spectrum and 13.0 at 20, complex64.)
 bool block_pays(int dtype, int tp, int log2c, bool pol, int64_t units, int64_t S)
 {
     if (!block_supported(dtype, tp, log2c, pol))
+        return false;
+    const bool ints = dtype == 1 || dtype == 2;
+    if (!pol && tp == 32 && log2c >= 6 && log2c <= 8 && units * S < (log2c == 7 && !ints ? 48 : 16))
         return false;
     const int64_t rows = block_rows(log2c, pol);
     const int64_t blocks = units * ((S + rows - 1) / rows);

@@ -60,3 +60,19 @@ result = [e for e in events() if "gh_partial" in e[0]]
     assert len(got) >= 1
     waves = B * -(-C // 64) * -(-S // rows)
     assert sum(n for _, n in got) <= -(-waves // 4) + len(got)
+
+
+@pytest.mark.parametrize("C,T,S,B,dtype,one", [
+    (128, 20, 1, 1, "C64", False), (128, 32, 47, 1, "CF16", False), (128, 32, 48, 1, "C64", True),
+    (128, 32, 15, 1, "CI8", False), (128, 17, 16, 1, "CI16", True), (128, 17, 5, 20, "C64", True),
+    (256, 30, 15, 1, "C64", False), (256, 30, 16, 1, "CI8", True), (64, 32, 8, 1, "CF16", False),
+    (32, 32, 1, 1, "C64", True), (128, 16, 1, 1, "C64", True)])
+def test_part_of_a_block_at_17_to_32_taps(tmp_path_factory, C, T, S, B, dtype, one):
+    """A handful of spectra take the two launches, not a whole block's time."""
+    got = host_run(tmp_path_factory, f"""
+p = plan({C}, {T}, {S}, {B}, {dtype})
+events()
+assert L.pfb_execute(p, A, A, None, A, None) == 0
+result = [e[0] for e in events()]
+""")
+    assert len(got) == (1 if one else 2) and ("block_kernel" in got[0]) == one
