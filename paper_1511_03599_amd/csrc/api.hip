@@ -664,7 +664,7 @@ static hipError_t run_fir(const pfb_plan *p, const void *x, const float *h, floa
     a.y_bstride = y_bstride;
     if (p->long_fir || p->fir_segments) {
         // up to 64 taps the padding leads, as in the register window
-        a.shift = p->long_fir ? 0 : (16 - d.taps % 16) % 16;
+        a.shift = p->long_fir ? 0 : (FIR_LONG_ROWS - d.taps % FIR_LONG_ROWS) % FIR_LONG_ROWS;
         return launch_fir_long(a, d.dtype, st);
     }
     return launch_fir(a, d.dtype, p->tp, p->fir_cpt, false, st, (d.flags & PFB_CONVERT_PER_USE) != 0);

@@ -31,7 +31,6 @@
 
 namespace pfb {
 
-constexpr int FIR_LONG_ROWS = 16;      // sums and window rows per lane, taps per segment
 constexpr unsigned FIR_LONG_GRID = 1 << 20; // workgroups along x (a dimension holds under 2^32 threads)
 
 // LEAD: a.shift zero taps come first (the counters that keep them and the rows

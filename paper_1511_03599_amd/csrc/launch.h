@@ -110,9 +110,12 @@ hipError_t launch_fir_ci16(const FirArgs &a, int tp, int cpt, bool per_use, hipS
 hipError_t launch_fir_ci8(const FirArgs &a, int tp, int cpt, bool per_use, hipStream_t st);
 hipError_t launch_fir_cf16(const FirArgs &a, int tp, int cpt, bool per_use, hipStream_t st);
 hipError_t launch_fir_adjoint(const FirArgs &a, int tp, int cpt, hipStream_t st); // reversed taps, c64
-// FIR for T beyond the register window: tiles of 32 rows (SB = 32), one
-// channel per lane (64 per wave task), no tap padding (shift = 0).
-hipError_t launch_fir_long(FirArgs a, int dtype, hipStream_t st); // sets its own tiles
+// FIR for T beyond the register window, and for 33 to 64 taps where that is
+// the faster one: one channel per lane (64 per wave task), tiles of
+// FIR_LONG_ROWS filtered spectra (a.SB and the counts are set here). a.shift
+// zero taps lead, fewer than FIR_LONG_ROWS.
+constexpr int FIR_LONG_ROWS = 16; // sums and window rows per lane, taps per segment
+hipError_t launch_fir_long(FirArgs a, int dtype, hipStream_t st);
 hipError_t launch_gh(const GhArgs &a, int tp, float *gh, hipStream_t st);
 // padded taps tp <= 32; also runs the reduction into gh
 hipError_t launch_gxgh(const GxGhArgs &a, int tp, float *gh, hipStream_t st);
