@@ -532,7 +532,7 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
             p->blocked = tuned && te.block >= 0 ? te.block != 0
                          : tuned && te.chunk_mib > 0
                              ? false
-                             : block_pays(d->dtype, p->tp, p->log2c, false, d->batch, d->spectra);
+                             : block_pays(d->dtype, p->tp, p->log2c, false, d->batch, d->spectra, p->num_cus);
         }
         if (p->blocked) {
             p->chunk_rows = block_rows(p->log2c, false);
@@ -871,7 +871,7 @@ extern "C" pfb_status pfb_plan_create_vegas(int32_t channels, int32_t subbands, 
         p->vegas_nsub = subbands;
         p->vegas_log2cv = l2;
         st = make_twiddles(l2, &p->twiddle);
-        p->blocked = !p->long_fir && block_pays(dtype, p->tp, l2, true, subbands, spectra) &&
+        p->blocked = !p->long_fir && block_pays(dtype, p->tp, l2, true, subbands, spectra, p->num_cus) &&
                      block_views_fit(d, block_rows(l2, true), p->tp);
     }
     if (st == PFB_OK && !p->blocked) {

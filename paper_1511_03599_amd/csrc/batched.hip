@@ -50,7 +50,7 @@ constexpr int BT_WAVES = BT_THREADS / 64;
 constexpr int BT_TASK_ROWS = 32;         // filtered spectra per FIR wave task
 constexpr int BT_LDS = 8704;             // float2: the largest transform round (one 8192-point row)
 constexpr int BT_MAX_TAPS = PFB_MAX_TAPS_WINDOW;
-constexpr int64_t BT_ALONE_SAMPLES = 1 << 22; // filtered samples from which a beam has a launch of its own
+constexpr int64_t BT_ALONE_SAMPLES = 1 << 14; // filtered samples per CU from which a beam has a launch of its own
 
 struct BeamInfo {
     const float2 *tw;      // twiddles for C
@@ -393,11 +393,11 @@ static pfb_status build_batched(int32_t nbeams, const pfb_desc *beams, Batched *
         // Long windows at 2048 channels and more gain less, on 4 M samples
         // nothing (4096 channels, 32 taps, 10 beams of 4 M 392 -> 447 us;
         // other sizes 258 -> 155, 269 -> 190, 436 -> 276).
-        const int64_t line = bi.TP >= 32 && bi.log2c >= 11 ? 4 * BT_ALONE_SAMPLES : BT_ALONE_SAMPLES;
+        const int64_t line = B->num_cus * BT_ALONE_SAMPLES * (bi.TP >= 32 && bi.log2c >= 11 ? 4 : 1);
         if (d.spectra * d.channels >= line) {
             if (fused_supported(DT_C64, bi.TP, bi.log2c))
                 B->fused_rows[(size_t)i] = pfb_internal_fused_tile_rows(1, d.spectra, d.taps, bi.log2c, B->num_cus);
-            else if (block_pays(DT_C64, bi.TP, bi.log2c, false, 1, d.spectra))
+            else if (block_pays(DT_C64, bi.TP, bi.log2c, false, 1, d.spectra, B->num_cus))
                 B->fused_rows[(size_t)i] = 0;
         }
         if (B->fused_rows[(size_t)i] >= 0)

@@ -37,7 +37,8 @@ int block_rows(int log2c, bool pol)
 // (4096 channels, 32 taps), and a launch of few blocks leaves the other CUs
 // idle, where the FIR and FFT launches spread over more of them. Split over
 // blocked time, on 256 CUs, at 64 and 128 blocks and where noted 32 or 256;
-// a line between two measured counts is where the time interpolates to equal:
+// a line between two measured counts is where the time interpolates to equal,
+// and it is in blocks per CU (a partition of the card has fewer):
 //   2048 channels, 16 taps        complex64 0.90, 1.25; int8 0.95, 1.46
 //   4096 channels, 8 taps         0.97, 1.23
 //   1024 channels, 32 taps        0.83, 1.35
@@ -57,7 +58,7 @@ int block_rows(int log2c, bool pol)
 // rows of a ragged tile); 256 channels 5 spectra 9.5, 12.9, 16 spectra 13.3,
 // 12.9; 32 channels 32 spectra 15.7, 12.2. (With FIR tiles of 128 rows the
 // split path took 12.2 at 1 spectrum and 13.0 at 20, complex64.)
-bool block_pays(int dtype, int tp, int log2c, bool pol, int64_t units, int64_t S)
+bool block_pays(int dtype, int tp, int log2c, bool pol, int64_t units, int64_t S, int cus)
 {
     if (!block_supported(dtype, tp, log2c, pol))
         return false;
@@ -66,7 +67,7 @@ bool block_pays(int dtype, int tp, int log2c, bool pol, int64_t units, int64_t S
         return false;
     const int64_t rows = block_rows(log2c, pol);
     const int64_t blocks = units * ((S + rows - 1) / rows);
-    int64_t from = 1;
+    int from = 1;
     if (pol)
         from = log2c <= 9 ? 1 : tp >= 32 ? 112 : 72;
     else if (tp == 64)
@@ -75,7 +76,7 @@ bool block_pays(int dtype, int tp, int log2c, bool pol, int64_t units, int64_t S
         from = tp == 32 ? 60 : 1;
     else if (log2c >= 10)
         from = log2c >= 11 && (tp >= 32 || (log2c == 13 && tp == 16)) ? 160 : 84;
-    return blocks >= from;
+    return 256 * blocks >= (int64_t)from * cus;
 }
 
 hipError_t launch_block(const BlockArgs &a, int dtype, int tp, int log2c, bool pol, hipStream_t st)

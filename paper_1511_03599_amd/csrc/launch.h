@@ -165,7 +165,7 @@ PFB_BLOCK_DECL(cf16)
 hipError_t launch_block(const BlockArgs &a, int dtype, int tp, int log2c, bool pol, hipStream_t st);
 bool block_supported(int dtype, int tp, int log2c, bool pol);
 int block_rows(int log2c, bool pol); // filtered spectra per block
-bool block_pays(int dtype, int tp, int log2c, bool pol, int64_t units, int64_t S);
+bool block_pays(int dtype, int tp, int log2c, bool pol, int64_t units, int64_t S, int cus);
 hipError_t launch_fused_ws(const FusedArgs &a, int dtype, int tp, int log2c, hipStream_t st);
 // nblk blocks of `bytes` bytes from src + b*src_stride to dst + b*dst_stride
 // (src NULL: zeros).

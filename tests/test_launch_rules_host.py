@@ -76,3 +76,28 @@ assert L.pfb_execute(p, A, A, None, A, None) == 0
 result = [e[0] for e in events()]
 """)
     assert len(got) == (1 if one else 2) and ("block_kernel" in got[0]) == one
+
+
+@pytest.mark.parametrize("cus,blocks,one", [(256, 83, False), (256, 84, True), (32, 10, False), (32, 11, True)])
+def test_lines_scale_with_the_compute_units(tmp_path_factory, cus, blocks, one):
+    """The blocked kernel's lines are in blocks per compute unit (2048
+    channels, 16 taps; sub-bands of 1024 channels from 72 for 256), and so is
+    a beam's size for a launch of its own (here always the fused one)."""
+    got = host_run(tmp_path_factory, f"""
+rt.host_cus({cus})
+def launches(f):
+    events()
+    assert f() == 0
+    return [e[0] for e in events()]
+p = plan(2048, 16, {blocks} * 16)
+result = [launches(lambda: L.pfb_execute(p, A, A, None, A, None))]
+v = vp()
+assert L.pfb_plan_create_vegas(1024, 1, 16, {blocks - 12 if cus == 256 else blocks - 2} * 16, C64, ctypes.byref(v)) == 0
+result.append(launches(lambda: L.pfb_execute_vegas(v, A, A, A, None)))
+b, P = vp(), vp * 1
+assert L.pfb_plan_create_batched(1, ctypes.byref(Desc(1024, 16, {16 * cus - (0 if one else 1)}, 1, C64, 0)), ctypes.byref(b)) == 0
+result.append(launches(lambda: L.pfb_execute_batched(b, P(A.value), P(A.value), P(A.value), None)))
+""")
+    assert (len(got[0]) == 1 and "block_kernel" in got[0][0]) == one
+    assert (len(got[1]) == 1 and "block_kernel" in got[1][0]) == one
+    assert (len(got[2]) == 1 and "fused_fwd" in got[2][0]) == one
