@@ -463,6 +463,8 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
     const bool cpt2_ok = p->tp <= 16 && d->channels % 2 == 0;
     const bool wide_one = (d->dtype == PFB_C64 && d->channels >= 2048) || (d->dtype == PFB_CI8 && d->channels >= 4096);
     p->fir_cpt = cpt2_ok && !wide_one ? 2 : 1;
+    if (tuned && (te.fir_cpt == 1 || (te.fir_cpt == 2 && cpt2_ok)))
+        p->fir_cpt = te.fir_cpt;
     // Integer input at 32 taps runs its unconditional block on tiles of one
     // block only (several would not fit the registers), so 32 rows where
     // every lane has a channel: 1024 channels, 65536 spectra int8 256 -> 178
@@ -474,17 +476,16 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
                                                                      : 32;
     // Launches of fewer waves than fit at once (eight a CU): shorter tiles
     // (1024 channels, 16 taps, 1000 spectra 9.3 -> 7.0 us; 32 taps, 2000
-    // spectra 51 -> 14). A plan with a tuned entry keeps the heights above.
+    // spectra 51 -> 14). With an entry carried over from another length plans
+    // of up to 16 taps keep the heights above (900 spectra, one channel per
+    // lane 7.0 us, with 16 rows 5.9).
     const double waves_per_row = (double)d->batch * (double)ceil_div(d->channels, 64 * p->fir_cpt);
-    if (!tuned && p->tp <= 32 && waves_per_row * (double)ceil_div(d->spectra, p->fir_sb) < 8.0 * p->num_cus)
+    const bool shorten = p->tp == 32 || (p->tp <= 16 && !(tuned && te.carried));
+    if (shorten && waves_per_row * (double)ceil_div(d->spectra, p->fir_sb) < 8.0 * p->num_cus)
         p->fir_sb = p->tp <= 16 ? 16 : 32;
     p->fir_segments = !tuned && fir_segments_pay(*d, p->num_cus);
-    if (tuned) {
-        if (te.fir_cpt == 1 || (te.fir_cpt == 2 && cpt2_ok))
-            p->fir_cpt = te.fir_cpt;
-        if (te.fir_sb >= 16 && te.fir_sb <= 8192)
-            p->fir_sb = te.fir_sb;
-    }
+    if (tuned && te.fir_sb >= 16 && te.fir_sb <= 8192)
+        p->fir_sb = te.fir_sb;
     if (d->flags & PFB_PLAIN) {
         // the untuned comparator: one channel per lane, long tiles
         p->fir_cpt = 1;

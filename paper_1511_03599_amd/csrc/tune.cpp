@@ -120,6 +120,7 @@ bool tune_lookup(const pfb_desc &d, TuneEntry *out)
         e.fir_cpt = best_near.fir_cpt;
         e.fused_ws = best_near.fused_ws;
         e.bwd_ws = best_near.bwd_ws;
+        e.carried = true;
         *out = e;
         return true;
     }

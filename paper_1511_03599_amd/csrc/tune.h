@@ -19,6 +19,7 @@ struct TuneEntry {
     int block = -1;      // split path: 1 FIR and FFT in one launch, block by block, 0 two launches, -1 not set
     int bwd_sb = 0;      // fused adjoint rows per tile
     int bwd_ws = -1;     // fused adjoint: 1 wave-specialised, 0 single-role, -1 not set
+    bool carried = false; // from an entry of another length
 };
 
 // Look the descriptor up in the cache file named by PFB_TUNE_CACHE. Returns
