@@ -400,6 +400,11 @@ static int tap_gradient_rows(const pfb_desc &d, int tp, int cus)
     return best;
 }
 
+static bool fir_segments_supported(const pfb_desc &d)
+{
+    return d.taps > 32 && d.taps <= PFB_MAX_TAPS_WINDOW && !(d.flags & (PFB_PLAIN | PFB_CONVERT_PER_USE));
+}
+
 // Whether 33 to 64 taps run faster through the long-tap FIR (16-row tiles,
 // taps rounded up to 16) than through the 64-tap register window (64-row
 // tiles, at most eight waves a CU). In us, for a round of eight 64-row tiles
@@ -411,7 +416,7 @@ static int tap_gradient_rows(const pfb_desc &d, int tp, int cus)
 // 31 -> 13, 38 -> 14; 98 (102), 99 -> 85; 301 (407), 255 (278).
 static bool fir_segments_pay(const pfb_desc &d, int cus)
 {
-    if (d.taps <= 32 || d.taps > PFB_MAX_TAPS_WINDOW || (d.flags & (PFB_PLAIN | PFB_CONVERT_PER_USE)))
+    if (!fir_segments_supported(d))
         return false;
     const bool c64 = d.dtype == PFB_C64;
     const double rounds = (double)d.batch * (double)ceil_div(d.channels, 64) * (double)ceil_div(d.spectra, 64) / (8.0 * cus);
@@ -483,7 +488,8 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
     const bool shorten = p->tp == 32 || (p->tp <= 16 && !(tuned && te.carried));
     if (shorten && waves_per_row * (double)ceil_div(d->spectra, p->fir_sb) < 8.0 * p->num_cus)
         p->fir_sb = p->tp <= 16 ? 16 : 32;
-    p->fir_segments = !tuned && fir_segments_pay(*d, p->num_cus);
+    p->fir_segments = tuned && te.segments >= 0 ? te.segments != 0 && fir_segments_supported(*d)
+                                                : fir_segments_pay(*d, p->num_cus);
     if (tuned && te.fir_sb >= 16 && te.fir_sb <= 8192)
         p->fir_sb = te.fir_sb;
     if (d->flags & PFB_PLAIN) {
@@ -1075,6 +1081,7 @@ int pfb_internal_bwd_tile_rows(int64_t B, int64_t S, int T, int C, int cus)
     const int sb = adjoint_tile_rows(B, S + T - 1, T, C, cus);
     return std::min(sb, view_rows_cap((int64_t)C * 8, 16, 0));
 }
+bool pfb_internal_fir_segments(const pfb_desc *d) { return fir_segments_supported(*d); }
 pfb_status pfb_internal_validate(const pfb_desc *d, bool batched_beam) { return validate_desc(d, batched_beam); }
 pfb_plan *pfb_internal_new_plan() { return new (std::nothrow) pfb_plan(); }
 void pfb_internal_set_batched(pfb_plan *p, Batched *b) { p->kind = KIND_BATCHED; p->batched = b; }

@@ -1,6 +1,6 @@
 // Tuning cache: a small text file, one entry per line,
 //   <arch> <dtype> <C> <T> <B> <S> path=<p> fir_cpt=<n> fir_sb=<n> fused_sb=<n> fused_ws=<n> chunk_mib=<n>
-//   bwd_sb=<n> bwd_ws=<n> block=<n>
+//   bwd_sb=<n> bwd_ws=<n> block=<n> segments=<n>
 // for single plans, and
 //   <arch> batched <nbeams> <total samples> tile_kib=<n>
 // for batched plans.
@@ -96,6 +96,7 @@ bool tune_lookup(const pfb_desc &d, TuneEntry *out)
             parse_kv(tok, "bwd_sb", &e.bwd_sb);
             parse_kv(tok, "bwd_ws", &e.bwd_ws);
             parse_kv(tok, "block", &e.block);
+            parse_kv(tok, "segments", &e.segments);
         }
         if (B == d.batch && S == d.spectra) {
             best_exact = e; // the last matching line wins
@@ -292,18 +293,18 @@ extern "C" pfb_status pfb_tune(const pfb_desc *desc, const char *cache_path)
         for (int cpt : {1, 2}) {
             if (cpt == 2 && !cpt2)
                 continue;
-            for (int sb : {16, 32, 64, 128}) {
+            for (int sb : {16, 32, 64, 128, 0}) { // 0: the long-tap FIR, whose tiles have one height
+                if (sb == 0 && !pfb_internal_fir_segments(&d))
+                    continue;
+                TuneEntry e;
+                e.fir_cpt = cpt;
+                e.fir_sb = sb;
+                e.segments = sb == 0;
                 if (path == 2) {
-                    TuneEntry e;
-                    e.fir_cpt = cpt;
-                    e.fir_sb = sb;
                     cands.push_back(e);
                 } else {
                     for (int mib : {0, 64, 256, 1024}) { // 0: one chunk
-                        TuneEntry e;
                         e.path = 1;
-                        e.fir_cpt = cpt;
-                        e.fir_sb = sb;
                         e.chunk_mib = mib;
                         e.block = 0;
                         cands.push_back(e);
@@ -344,8 +345,8 @@ extern "C" pfb_status pfb_tune(const pfb_desc *desc, const char *cache_path)
     for (const TuneEntry &e : cands) {
         const double t = time_candidate(d, e, buf, s, reps);
         if (verbose)
-            std::fprintf(stderr, "pfb_tune: path=%d fir_cpt=%d fir_sb=%d fused_ws=%d fused_sb=%d chunk_mib=%d block=%d -> %.4f ms\n",
-                         e.path, e.fir_cpt, e.fir_sb, e.fused_ws, e.fused_sb, e.chunk_mib, e.block, t);
+            std::fprintf(stderr, "pfb_tune: path=%d fir_cpt=%d fir_sb=%d fused_ws=%d fused_sb=%d chunk_mib=%d block=%d segments=%d -> %.4f ms\n",
+                         e.path, e.fir_cpt, e.fir_sb, e.fused_ws, e.fused_sb, e.chunk_mib, e.block, e.segments, t);
         if (t > 0 && (best_t < 0 || t < best_t)) {
             best_t = t;
             best = e;
@@ -385,10 +386,10 @@ extern "C" pfb_status pfb_tune(const pfb_desc *desc, const char *cache_path)
         return pfb_internal_fail(PFB_E_INVALID, "cannot open the tuning cache for writing");
     std::fprintf(f,
                  "%s %d %d %d %d %lld path=%d fir_cpt=%d fir_sb=%d fused_sb=%d fused_ws=%d chunk_mib=%d bwd_sb=%d "
-                 "bwd_ws=%d block=%d ms=%.5f\n",
+                 "bwd_ws=%d block=%d segments=%d ms=%.5f\n",
                  device_arch_name().c_str(), d.dtype, d.channels, d.taps, d.batch, (long long)d.spectra, best.path,
                  best.fir_cpt, best.fir_sb, best.fused_sb, best.fused_ws, best.chunk_mib, best.bwd_sb, best.bwd_ws,
-                 best.block, best_t);
+                 best.block, best.segments, best_t);
     std::fclose(f);
     return PFB_OK;
 }

@@ -17,6 +17,7 @@ struct TuneEntry {
     int fused_ws = -1;   // fused forward: 1 wave-specialised, 0 single-role, -1 not set
     int chunk_mib = 0;   // split-path chunk size
     int block = -1;      // split path: 1 FIR and FFT in one launch, block by block, 0 two launches, -1 not set
+    int segments = -1;   // 33 to 64 taps: 1 the long-tap FIR, 0 the register window, -1 not set
     int bwd_sb = 0;      // fused adjoint rows per tile
     int bwd_ws = -1;     // fused adjoint: 1 wave-specialised, 0 single-role, -1 not set
     bool carried = false; // from an entry of another length
@@ -49,6 +50,7 @@ constexpr int BATCHED_TILE_KIB_DEFAULT = 256;
 struct Batched;
 void batched_free(Batched *b);
 
+bool pfb_internal_fir_segments(const pfb_desc *d);
 pfb_status pfb_internal_fail(pfb_status st, const char *msg);
 int pfb_internal_fused_tile_rows(int64_t B, int64_t S, int T, int log2c, int cus);
 int pfb_internal_bwd_tile_rows(int64_t B, int64_t S, int T, int C, int cus);

@@ -29,3 +29,60 @@ def test_short_launches_keep_short_tiles_beside_an_entry(tmp_path_factory, tmp_p
 def test_heights_up_to_16_taps_beside_an_entry(tmp_path_factory, tmp_path, line, rows):
     got = plans_with(tmp_path_factory, tmp_path, [line], "result = info(plan(1024, 16, 900, flags=FIR_ONLY)).fir_rows")
     assert got == rows
+
+
+TUNE = """
+import os
+cache = os.environ["PFB_TUNE_CACHE"]
+os.environ.pop("PFB_TUNE_CACHE")
+d = Desc({C}, {T}, {S}, 1, {dtype}, {flags})
+rt.host_time({kernel!r}.encode(), ctypes.c_float({ms}))
+assert L.pfb_tune(ctypes.byref(d), cache.encode()) == 0
+events()
+libc = ctypes.CDLL(None)
+libc.setenv(b"PFB_TUNE_CACHE", cache.encode(), 1)
+p = plan({C}, {T}, {S}, 1, {dtype}, {flags})
+events()
+Y = None if {flags} & FIR_ONLY else A
+assert L.pfb_execute(p, A, A, A if {flags} & FIR_ONLY else None, Y, None) == 0
+result = dict(launches=events(), line=dict(f.split("=") for f in open(cache).read().split()[6:]), rows=info(p).fir_rows)
+"""
+
+
+def tuned(tmp_path_factory, tmp_path, **kw):
+    """Tune with every launch taking 1 ms but those of `kernel`, then what a
+    plan with that cache launches."""
+    return host_run(tmp_path_factory, TUNE.format(**{"dtype": "C64", "flags": "0", "ms": 0.5, **kw}),
+                    {"PFB_TUNE_CACHE": str(tmp_path / "tuned.txt")})
+
+
+@pytest.mark.parametrize("T,flags", [(33, "FIR_ONLY"), (48, "FIR_ONLY"), (64, "FIR_ONLY"), (48, "NO_FUSE")])
+def test_tuner_can_choose_the_long_tap_fir(tmp_path_factory, tmp_path, T, flags):
+    got = tuned(tmp_path_factory, tmp_path, C=256, T=T, S=3000, flags=flags, kernel="fir_long_kernel")
+    assert "fir_long_kernel" in got["launches"][0][0] and got["line"]["segments"] == "1"
+    (tmp_path / "tuned.txt").unlink()
+    got = tuned(tmp_path_factory, tmp_path, C=256, T=T, S=3000, flags=flags, kernel="fir_long_kernel", ms=2.0)
+    assert "fir_long_kernel" not in got["launches"][0][0] and got["line"]["segments"] == "0"
+
+
+@pytest.mark.parametrize("line,long", [
+    ("gfx950 0 256 48 1 3000 fir_cpt=1 fir_sb=64 segments=0", False),
+    ("gfx950 0 256 48 1 3000 fir_cpt=1 segments=1", True),
+    ("gfx950 0 256 48 1 3000 fir_cpt=1 fir_sb=64", True),        # written without the choice: the rule
+    ("gfx950 0 256 48 1 2900 fir_cpt=1 fir_sb=64 segments=0", True),  # another length: the rule
+])
+def test_long_tap_fir_beside_an_entry(tmp_path_factory, tmp_path, line, long):
+    got = plans_with(tmp_path_factory, tmp_path, [line], """
+p = plan(256, 48, 3000, flags=FIR_ONLY)
+events()
+assert L.pfb_execute(p, A, A, A, None, None) == 0
+result = events()[0][0]
+""")
+    assert ("fir_long_kernel" in got) == long
+    plain = plans_with(tmp_path_factory, tmp_path, ["gfx950 0 256 48 1 3000 segments=1"], """
+p = plan(256, 48, 3000, flags=FIR_ONLY | PLAIN)
+events()
+assert L.pfb_execute(p, A, A, A, None, None) == 0
+result = events()[0][0]
+""")
+    assert "fir_long_kernel" not in plain
