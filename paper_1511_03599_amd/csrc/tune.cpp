@@ -334,14 +334,12 @@ extern "C" pfb_status pfb_tune(const pfb_desc *desc, const char *cache_path)
             TuneEntry e;
             e.path = 1;
             e.block = 1;
-            e.fir_cpt = cpt2 ? 2 : 1; // of calls that keep the filtered spectra
-            e.fir_sb = 32;
             cands.push_back(e);
         }
     }
     const int reps = 7;
-    double best_t = -1.0;
-    TuneEntry best;
+    double best_t = -1.0, two_t = -1.0;
+    TuneEntry best, two; // two: the fastest of two launches
     for (const TuneEntry &e : cands) {
         const double t = time_candidate(d, e, buf, s, reps);
         if (verbose)
@@ -351,6 +349,17 @@ extern "C" pfb_status pfb_tune(const pfb_desc *desc, const char *cache_path)
             best_t = t;
             best = e;
         }
+        if (e.block == 0 && t > 0 && (two_t < 0 || t < two_t)) {
+            two_t = t;
+            two = e;
+        }
+    }
+    if (best.block == 1) {
+        // calls that keep the filtered spectra, and the adjoint's FIR, run
+        // the two launches
+        best.fir_cpt = two.fir_cpt;
+        best.fir_sb = two.fir_sb;
+        best.segments = two.segments;
     }
     if (best_t < 0)
         return pfb_internal_fail(PFB_E_HIP, "no tuning candidate ran");

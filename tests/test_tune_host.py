@@ -86,3 +86,15 @@ assert L.pfb_execute(p, A, A, A, None, None) == 0
 result = events()[0][0]
 """)
     assert "fir_long_kernel" not in plain
+
+
+def test_blocked_choice_keeps_the_timed_fir(tmp_path_factory, tmp_path):
+    """Where the blocked kernel wins, the FIR of the other calls is the one
+    that was fastest in two launches (all take the same time here: the first
+    one timed), not an untimed height."""
+    got = tuned(tmp_path_factory, tmp_path, C=256, T=48, S=3000, kernel="block_kernel", ms=0.25)
+    assert got["line"]["block"] == "1" and "block_kernel" in got["launches"][0][0]
+    assert got["line"]["fir_cpt"] == "1" and got["line"]["fir_sb"] == "16" and got["line"]["segments"] == "0"
+    (tmp_path / "tuned.txt").unlink()
+    got = tuned(tmp_path_factory, tmp_path, C=4096, T=4, S=3000, kernel="block_kernel", ms=0.25)
+    assert got["line"]["block"] == "1" and got["line"]["fir_sb"] == "16"
