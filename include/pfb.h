@@ -128,7 +128,8 @@ typedef struct {
                               chip (same bits); 2 FIR only                  */
     int32_t fir_rows;      /* filtered spectra per FIR tile (S_B)              */
     int32_t fir_cpt;       /* channels per thread in the FIR kernel            */
-    int32_t padded_taps;   /* taps rounded up to the kernel's template size    */
+    int32_t padded_taps;   /* taps rounded up to the kernel's template size, or
+                              to the long-tap FIR's segments of 16            */
     int64_t workspace_bytes;
     int64_t chunk_rows;    /* spectra per FIR/FFT chunk on the split path (per
                               block where one launch runs both)            */

@@ -632,9 +632,10 @@ extern "C" pfb_status pfb_plan_get_info(const pfb_plan *p, pfb_plan_info *info)
     if (p->kind != KIND_SINGLE)
         return fail(PFB_E_STATE, "not a single-problem plan");
     info->path = (int32_t)p->path;
-    info->fir_rows = p->path == PATH_FUSED ? p->fused_sb : p->fir_sb;
-    info->fir_cpt = p->fir_cpt;
-    info->padded_taps = p->tp;
+    const bool seg = p->long_fir || p->fir_segments;
+    info->fir_rows = p->path == PATH_FUSED ? p->fused_sb : seg ? FIR_LONG_ROWS : p->fir_sb;
+    info->fir_cpt = seg ? 1 : p->fir_cpt;
+    info->padded_taps = seg ? (int32_t)ceil_div(p->d.taps, FIR_LONG_ROWS) * FIR_LONG_ROWS : p->tp;
     info->workspace_bytes = p->ws_y_bytes + p->ws_gy_bytes + p->ws_gh_bytes;
     info->backward_fused = p->bwd_fused ? (p->bwd_ws ? 2 : 1) : 0;
     info->fused_ws = (p->path == PATH_FUSED && p->fused_ws) ? 1 : 0;
