@@ -139,8 +139,10 @@ typedef struct {
                               wave-specialised form (same results)          */
     int32_t fused_ws;      /* 1 if the fused forward runs its wave-specialised
                               form (same results as the single-role kernel)  */
-    int32_t backward_rows; /* sample-gradient rows per adjoint tile (fused
-                              adjoint) or per adjoint FIR tile (split)      */
+    int32_t backward_rows; /* sample-gradient rows per adjoint tile: of the
+                              fused adjoint, of the split adjoint's combined
+                              pass (both gradients, up to 32 taps), or of its
+                              FIR (above 32 taps)                           */
 } pfb_plan_info;
 
 /*

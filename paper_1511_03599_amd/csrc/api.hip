@@ -640,7 +640,9 @@ extern "C" pfb_status pfb_plan_get_info(const pfb_plan *p, pfb_plan_info *info)
     info->backward_fused = p->bwd_fused ? (p->bwd_ws ? 2 : 1) : 0;
     info->fused_ws = (p->path == PATH_FUSED && p->fused_ws) ? 1 : 0;
     info->chunk_rows = p->chunk_rows;
-    info->backward_rows = p->bwd_fused ? p->bwd_sb : p->fir_sb;
+    // the combined pass serves up to 32 taps (other input types have no adjoint)
+    const bool combined = p->ws_gy && p->tp <= 32;
+    info->backward_rows = p->bwd_fused ? p->bwd_sb : combined ? p->gh_sb : p->fir_sb;
     return PFB_OK;
 }
 

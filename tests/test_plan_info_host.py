@@ -21,3 +21,17 @@ result = [events()[0], i.fir_rows, i.padded_taps, i.fir_cpt]
     assert (fir_rows, padded) == (rows, taps)
     assert groups == -(-(-(-S // fir_rows)) * -(-C // (64 * cpt)) // 4)
     assert ("fir_long_kernel" in kernel) == (rows == 16)
+
+
+@pytest.mark.parametrize("C,T,S,B", [(128, 16, 4000, 3), (4096, 16, 8192, 2), (1024, 32, 16384, 1), (96, 5, 30, 1),
+                                     (1024, 40, 3000, 1)])
+def test_backward_rows_of_the_split_adjoint(tmp_path_factory, C, T, S, B):
+    got = host_run(tmp_path_factory, f"""
+p = plan({C}, {T}, {S}, {B})
+events()
+assert L.pfb_backward(p, A, A, A, A, A, None) == 0
+result = [[e for e in events() if "gxgh" in e[0] or "fir_kernel" in e[0]], info(p).backward_rows]
+""")
+    (((kernel, groups),), rows) = got
+    assert ("gxgh" in kernel) == (T <= 32)
+    assert groups == -(-(B * -(-(S + T - 1) // rows) * -(-C // 64)) // 4)
