@@ -597,6 +597,8 @@ extern "C" pfb_status pfb_execute_batched(pfb_plan *p, const void *const *x, con
         return PFB_OK;
     bool changed = false;
     for (int i = 0; i < B->nbeams; ++i) {
+        if (B->fused_rows[(size_t)i] >= 0)
+            continue; // launched above with this call's pointers
         const BeamPtrs &op = B->last_ptrs[(size_t)i];
         if (x[i] != op.x || taps[i] != op.h || Y[i] != (void *)op.Y)
             changed = true;

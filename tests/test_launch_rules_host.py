@@ -101,3 +101,23 @@ result.append(launches(lambda: L.pfb_execute_batched(b, P(A.value), P(A.value), 
     assert (len(got[0]) == 1 and "block_kernel" in got[0][0]) == one
     assert (len(got[1]) == 1 and "block_kernel" in got[1][0]) == one
     assert (len(got[2]) == 1 and "fused_fwd" in got[2][0]) == one
+
+
+def test_new_buffers_of_a_beam_with_its_own_launch(tmp_path_factory):
+    """They need no new pointer table, so no wait for the call before; new
+    buffers of a beam of the persistent launch do."""
+    got = host_run(tmp_path_factory, """
+P = vp * 2
+beams = (Desc * 2)(Desc(1024, 16, 4096, 1, C64, 0), Desc(64, 4, 100, 1, C64, 0))
+b = vp()
+assert L.pfb_plan_create_batched(2, beams, ctypes.byref(b)) == 0
+def call(big, small):
+    events()
+    assert L.pfb_execute_batched(b, P(big, small), P(A.value, A.value), P(big, small), None) == 0
+    return [e[0] if e[0] in ("wait", "copy", "graph") else "launch" for e in events()]
+a = A.value
+result = [call(a, a), call(a, a), call(a + 4096, a), call(a + 4096, a + 4096)]
+""")
+    first, same, big, small = got
+    assert first == ["launch", "copy", "graph"] and same == big == ["launch", "graph"]
+    assert small == ["launch", "wait", "copy", "graph"]
