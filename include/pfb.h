@@ -179,7 +179,8 @@ pfb_status pfb_execute(pfb_plan *plan, const void *x, const float *taps, void *y
  *         spectra (so the new data are never copied). The caller may reuse
  *         the same buffer on every call.
  *   taps, y, Y  as for pfb_execute (S filtered / frequency spectra per call).
- * After the call the plan keeps the last T-1 rows of xbuf per stream.
+ * After the call the plan keeps the last T-1 rows of xbuf per stream; a call
+ * that fails leaves the spectra carried before it.
  * Calls on one plan must be ordered (same stream, or synchronised).
  * Errors: PFB_E_STATE for a plan without PFB_STREAMING; otherwise those of
  * pfb_execute.

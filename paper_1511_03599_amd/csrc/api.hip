@@ -824,6 +824,13 @@ extern "C" pfb_status pfb_execute_stream(pfb_plan *p, void *xbuf, const float *t
             return hip_fail(e, "streaming history copy-in");
     }
     pfb_status r = pfb_execute(p, xbuf, taps, y, Y, stream);
+    if (r != PFB_OK && head > 0 && rotate) {
+        // a failed call leaves the carried spectra as they were: the
+        // headroom holds them
+        const std::string why = g_last_error;
+        (void)launch_copy_blocks(xb, stream_bytes, p->hist, head, head, d.batch, st);
+        return fail(r, why);
+    }
     if (r != PFB_OK || head == 0 || rotate)
         return r;
     // the last T-1 rows of every stream become the carried spectra
