@@ -82,3 +82,29 @@ def test_blocked_subbands_equal_streams(dev, CV, NS, T, S, dtype):
         for pol in range(2):
             ref = plan.execute(x[:, sub, :, pol].contiguous()[None], h)
             assert torch.equal(Y[:, sub, :, pol], ref[0]), (sub, pol)
+
+
+@pytest.mark.parametrize("CV", [512, 1024, 2048, 4096])
+@pytest.mark.parametrize("T", [3, 7, 13, 32])
+def test_blocked_subbands_every_window_and_type(dev, CV, T):
+    """Past the line (112 blocks) in every input type, the last block ragged;
+    a blocked sub-band plan has no workspace."""
+    import ctypes
+    import torch
+    from paper_1511_03599_amd import pfb
+    NS, rows = 8, 16384 // CV * (2 if CV >= 1024 else 1) // 2
+    S = 14 * rows - 1
+    h = taps_to_device(synth.random_taps(CV, T, 2851), dev)
+    for dtype in ("c64", "ci16", "ci8", "cf16"):
+        say(f"blocked sub-bands C_V={CV} T={T} S={S} {dtype}")
+        x = synth.device_quantised_noise((S + T - 1, NS, CV, 2), dtype, 2850 + CV + T, dev)
+        vegas = pfb.VegasPlan(CV, NS, T, S, dtype)
+        info = pfb.PlanInfo()
+        pfb.check(pfb.lib().pfb_plan_get_info(vegas._h, ctypes.byref(info)))
+        assert info.workspace_bytes == 0
+        Y = vegas.execute(x, h)
+        plan = pfb.Plan(CV, T, S, 1, dtype, pfb.NO_FUSE)
+        for sub in (0, NS - 1):
+            for pol in range(2):
+                ref = plan.execute(x[:, sub, :, pol].contiguous()[None], h)
+                assert torch.equal(Y[:, sub, :, pol], ref[0]), (dtype, sub, pol)

@@ -92,3 +92,27 @@ def test_mixed_radix_schedules(dev, C, S):
 @pytest.mark.parametrize("C,S", [(125, 33), (147, 15), (175, 17), (252, 5), (343, 9), (441, 6)])
 def test_mixed_radix_rows_off_the_lines(dev, C, S):
     test_mixed_radix_schedules(dev, C, S)
+
+
+@pytest.mark.parametrize("T", [3, 9, 13, 16])
+@pytest.mark.parametrize("S", [127, 129, 300, 700])
+def test_tested_form_of_the_fused_tiles(dev, T, S, tmp_path, monkeypatch):
+    """Tiles of 128 rows at 1024 channels (the form that tests its rows) with
+    ragged last tiles, padded taps and rows before the stream."""
+    import torch
+    from paper_1511_03599_amd import pfb
+    C, B = 1024, 2
+    arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+    h = taps_to_device(synth.random_taps(C, T, 2921), dev)
+    for dtype in ("c64", "ci16", "ci8", "cf16"):
+        say(f"tested form T={T} S={S} {dtype}")
+        cache = tmp_path / f"{dtype}.txt"
+        cache.write_text(f"{arch} {pfb.DTYPE_CODES[dtype]} {C} {T} {B} {S} path=0 fused_ws=0 fused_sb=128\n")
+        monkeypatch.setenv("PFB_TUNE_CACHE", str(cache))
+        plan = pfb.Plan(C, T, S, B, dtype)
+        monkeypatch.delenv("PFB_TUNE_CACHE")
+        info = plan.info()
+        assert info["path"] == "fused" and info["fir_rows"] == 128 and not info["fused_ws"]
+        x = synth.device_quantised_noise((B, S + T - 1, C), dtype, 2920 + T + S, dev)
+        ref = pfb.Plan(C, T, S, B, dtype, pfb.NO_FUSE).execute(x, h)
+        assert torch.equal(plan.execute(x, h), ref), dtype
