@@ -125,7 +125,8 @@ typedef struct {
                               through the workspace or, for a whole forward
                               call of the sizes it covers, by one launch that
                               keeps the results of a block of spectra on the
-                              chip (same bits); 2 FIR only                  */
+                              chip (same bits for finite samples); 2 FIR
+                              only                                          */
     int32_t fir_rows;      /* filtered spectra per FIR tile (S_B)              */
     int32_t fir_cpt;       /* channels per thread in the FIR kernel            */
     int32_t padded_taps;   /* taps rounded up to the kernel's template size, or
@@ -161,7 +162,11 @@ pfb_status pfb_plan_create(const pfb_desc *desc, pfb_plan **out);
  *         filtered spectra are written there too (this forces the split
  *         path). With PFB_FIR_ONLY, y is required and Y is ignored.
  *   Y     device, [B][S][C] complex float32 (required unless FIR_ONLY)
- * Outputs are overwritten. Inputs are not modified.
+ * Outputs are overwritten. Inputs are not modified. Every path gives the same
+ * bits for finite samples. An infinity or NaN also reaches the spectra whose
+ * window, filled up with zero taps to the kernel's size, holds it: before the
+ * T rows up to 64 taps (to a power of two, or to a multiple of 16 where a
+ * launch of 33 to 64 taps takes the long-tap FIR), behind them above.
  */
 pfb_status pfb_execute(pfb_plan *plan, const void *x, const float *taps, void *y, void *Y,
                        void *stream);
@@ -264,7 +269,7 @@ pfb_status pfb_backward_noalloc(const pfb_desc *desc, const void *x, const float
  * into a HIP graph when the plan is created; large ones run as launches of
  * their own where that is faster, on the same stream. Each beam's result is
  * the forward filter bank of its descriptor (Alg. 1 then Eq. (2)),
- * bit-identical to a separate single-beam plan.
+ * bit-identical to a separate single-beam plan for finite samples.
  *   nbeams  >= 1; beams: host array of nbeams descriptors (batch must be 1,
  *           dtype C64; flags ignored)
  * The plan owns its tile table and one slot of filtered spectra per

@@ -9,8 +9,10 @@
 // that a segment starts with are those that the one before ended on, so a
 // tile reads each of its N + T - 1 raw rows once. Each sum takes its taps in
 // ascending order from one accumulator, so the result is the sequential sum a
-// single window of T taps would give (zero taps that fill a segment, a.shift
-// of them in front, the others behind, add exact zeros). Rows are shared by T / N tiles; the caches serve the re-reads.
+// single window of T taps would give. Zero taps fill the segments, a.shift of
+// them in front, the others behind: for finite samples they add exact zeros,
+// an infinity or NaN under one of them makes the sum NaN. Rows are shared by
+// T / N tiles; the caches serve the re-reads.
 //
 // Rows, taps and stores go through bounded views of one row's 64 channels,
 // empty outside the stream, the filter or the tile: every load is

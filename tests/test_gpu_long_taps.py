@@ -41,3 +41,40 @@ def test_33_to_64_taps_equal_the_register_window(dev, C, T, S, B, dtype):
     h = taps_to_device(synth.random_taps(C, T, 2201), dev)
     y = pfb.Plan(C, T, S, B, dtype, pfb.FIR_ONLY).execute(x, h)
     assert torch.equal(y, pfb.Plan(C, T, S, B, dtype, pfb.FIR_ONLY | pfb.PLAIN).execute(x, h))
+
+
+@pytest.mark.parametrize("C,T,before,after", [
+    (256, 40, 0, 24),    # register window and blocked kernel: 24 zero taps lead; long-tap FIR: 8
+    (256, 64, 0, 0),
+    (256, 65, 15, 0),    # long-tap FIR: 15 zero taps follow
+    (1000, 90, 6, 0),
+])
+def test_non_finite_samples_stay_within_the_padded_window(dev, C, T, before, after, tmp_path, monkeypatch):
+    """An infinity reaches the spectra whose T rows hold it, and at most those
+    whose window holds it under zero taps; the others have the same bits as
+    without it, on every path."""
+    import torch
+    from paper_1511_03599_amd import pfb
+    S, r = 400, 200
+    say(f"non-finite long taps C={C} T={T}")
+    x = synth.device_noise((1, S + T - 1, C), 2300 + C + T, dev)
+    h = taps_to_device(synth.random_taps(C, T, 2301), dev)
+    arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+    plans = [pfb.Plan(C, T, S, 1, "c64", flags) for flags in (0, pfb.NO_FUSE, pfb.PLAIN)]
+    if T <= 64:
+        for choice in ("block=1", "block=0 segments=0 fir_sb=64", "block=0 segments=1"):
+            cache = tmp_path / "tune.txt"
+            cache.write_text(f"{arch} 0 {C} {T} 1 {S} path=1 {choice}\n")
+            monkeypatch.setenv("PFB_TUNE_CACHE", str(cache))
+            plans.append(pfb.Plan(C, T, S, 1, "c64"))
+            monkeypatch.delenv("PFB_TUNE_CACHE")
+    bad = x.clone()
+    bad[0, r, 7] = float("inf")
+    finite = plans[0].execute(x, h)
+    for i, plan in enumerate(plans):
+        Y = plan.execute(bad, h)[0]
+        ok = torch.isfinite(Y.real).all(1) & torch.isfinite(Y.imag).all(1)
+        assert not ok[r - T + 1:r + 1].any(), i
+        lo, hi = r - T + 1 - before, r + 1 + after
+        assert ok[:lo].all() and ok[hi:].all(), i
+        assert torch.equal(Y[:lo], finite[0, :lo]) and torch.equal(Y[hi:], finite[0, hi:]), i
