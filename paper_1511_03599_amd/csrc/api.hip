@@ -408,20 +408,33 @@ static bool fir_segments_supported(const pfb_desc &d)
 // Whether 33 to 64 taps run faster through the long-tap FIR (16-row tiles,
 // taps rounded up to 16) than through the 64-tap register window (64-row
 // tiles, at most eight waves a CU). In us, for a round of eight 64-row tiles
-// a CU: the window takes whole rounds of 37 (complex64) or 35, the long-tap
-// FIR 38.5 or 31.7 up to 48 taps and 50 or 39 above, in proportion, and 6
-// for its first rows. Window -> long-tap, 48 taps: 256 channels, 3000 spectra
-// complex64 33 -> 10 us, int8 41 -> 12; 2048 channels, 9000 spectra 96 -> 85
-// and 97 -> 71; 1024 channels, 65536 spectra 318 (362) and 257 -> 227; 64 taps
-// 31 -> 13, 38 -> 14; 98 (102), 99 -> 85; 301 (407), 255 (278).
+// a CU. The window takes 37 (complex64) or 33 a round and 42 or 44 where the
+// last channel chunk is ragged and every row is tested; one round takes 38 or
+// 40 however full, the second adds at least half its time, later ones run
+// into each other. The long-tap FIR takes 5 and, in proportion, up to 48 taps
+// 46 a round for complex64, 37.5 (48 taps: 36) where a row has 2048 channels
+// or more, and 30 for the other types; above 48 taps 52, 46, and 37 (64 taps:
+// 33.5). Fitted to 326 shapes of 1 to 8192 channels: the choice costs at most
+// 3% more than the window (with whole rounds of the window, and one rate for
+// all widths of complex64, up to 23%: 256 channels, 35 taps, 201231 spectra
+// 226 us, long-tap 278). Window -> long-tap, 48 taps: 256 channels, 3000
+// spectra complex64 33 -> 8.4 us, int8 41 -> 12; 2048 channels int8 9000
+// spectra 85 -> 62, complex64 14684 spectra 129 -> 107; 1000 channels int8
+// 36970 spectra 212 -> 110; 64 taps, 1000 channels float16 56880 spectra 310
+// -> 245.
 static bool fir_segments_pay(const pfb_desc &d, int cus)
 {
     if (!fir_segments_supported(d))
         return false;
-    const bool c64 = d.dtype == PFB_C64;
+    const bool c64 = d.dtype == PFB_C64, ragged = d.channels % 64 != 0, wide = d.channels >= 2048;
     const double rounds = (double)d.batch * (double)ceil_div(d.channels, 64) * (double)ceil_div(d.spectra, 64) / (8.0 * cus);
-    const double per_round = d.taps <= 48 ? (c64 ? 38.5 : 31.7) : (c64 ? 50.0 : 39.0);
-    return 6.0 + per_round * rounds < 0.97 * (c64 ? 37.0 : 35.0) * std::ceil(rounds);
+    const double full = c64 ? (ragged ? 42.0 : 37.0) : (ragged ? 44.0 : 33.0);
+    const double window = rounds <= 1.0  ? (c64 ? 38.0 : 40.0)
+                          : rounds < 2.0 ? full * std::min(2.0, rounds + 0.45)
+                                         : full * (rounds + 0.9 / rounds);
+    const double per_round = d.taps <= 48 ? (!c64 ? 30.0 : !wide ? 46.0 : d.taps == 48 ? 36.0 : 37.5)
+                                          : (c64 ? (wide ? 46.0 : 52.0) : d.taps == 64 ? 33.5 : 37.0);
+    return 5.0 + per_round * rounds < 0.97 * window;
 }
 
 static int64_t row_bytes_in(const pfb_desc &d) { return (int64_t)d.channels * bytes_per_sample(d.dtype); }

@@ -121,3 +121,27 @@ result = [call(a, a), call(a, a), call(a + 4096, a), call(a + 4096, a + 4096)]
     first, same, big, small = got
     assert first == ["launch", "copy", "graph"] and same == big == ["launch", "graph"]
     assert small == ["launch", "wait", "copy", "graph"]
+
+
+@pytest.mark.parametrize("C,T,S,dtype,long", [
+    # window and long-tap FIR as measured, us
+    (256, 35, 201231, "C64", False),    # 226, 278
+    (1024, 33, 25246, "C64", False),    # 116, 128
+    (4096, 41, 8410, "C64", False),     # 143, 153
+    (8192, 57, 2442, "CI16", False),    # 82, 87
+    (256, 64, 55183, "C64", False),     # 69, 94
+    (256, 48, 3000, "C64", True),       # 33, 8
+    (2048, 48, 14684, "C64", True),     # 129, 107
+    (8192, 47, 1599, "C64", True),      # 75, 55
+    (2048, 47, 4513, "CI8", True),      # 52, 34
+    (4096, 35, 8000, "CF16", True),     # 125, 101 at 7645, int16
+    (1000, 64, 56880, "CF16", True),    # 310, 245
+])
+def test_long_tap_fir_where_it_is_the_faster(tmp_path_factory, C, T, S, dtype, long):
+    got = host_run(tmp_path_factory, f"""
+p = plan({C}, {T}, {S}, 1, {dtype}, FIR_ONLY)
+events()
+assert L.pfb_execute(p, A, A, A, None, None) == 0
+result = events()[0][0]
+""")
+    assert ("fir_long_kernel" in got) == long
