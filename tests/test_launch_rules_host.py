@@ -145,3 +145,17 @@ assert L.pfb_execute(p, A, A, A, None, None) == 0
 result = events()[0][0]
 """)
     assert ("fir_long_kernel" in got) == long
+
+
+@pytest.mark.parametrize("cus,blocks,groups", [(256, 165, 168), (256, 256, 256), (256, 300, 256), (256, 97, 104),
+                                               (304, 301, 304), (60, 57, 57), (60, 300, 60)])
+def test_blocked_grids_deal_runs_to_the_xcds(tmp_path_factory, cus, blocks, groups):
+    """A multiple of eight workgroups where the compute units allow it."""
+    got = host_run(tmp_path_factory, f"""
+rt.host_cus({cus})
+p = plan(128, 8, {blocks} * 128)
+events()
+assert L.pfb_execute(p, A, A, None, A, None) == 0
+result = events()[0]
+""")
+    assert "block_kernel" in got[0] and got[1] == groups
