@@ -159,3 +159,29 @@ assert L.pfb_execute(p, A, A, None, A, None) == 0
 result = events()[0]
 """)
     assert "block_kernel" in got[0] and got[1] == groups
+
+
+@pytest.mark.parametrize("C,T,dtype,blocks,one", [
+    # split / blocked time as measured at or beside that count
+    (4096, 16, "C64", 92, False),    # 0.85
+    (4096, 16, "C64", 100, True),    # 1.02
+    (4096, 16, "CI8", 84, True),     # 1.03
+    (4096, 32, "C64", 165, True), (4096, 32, "C64", 256, True),
+    (4096, 32, "C64", 257, False),   # 0.86
+    (4096, 32, "C64", 384, False),   # 0.96
+    (4096, 32, "C64", 420, True),
+    (4096, 24, "CI16", 300, False), (4096, 24, "CI16", 330, True),
+    (8192, 8, "C64", 92, False),     # 0.90
+    (8192, 16, "C64", 320, False), (8192, 16, "C64", 344, True), (8192, 16, "CI8", 257, False), (8192, 16, "CI8", 280, True),
+    (1024, 32, "CF16", 100, False), (1024, 32, "C64", 84, True),
+    (1024, 64, "CI8", 300, False),   # 0.89
+    (1024, 64, "CI8", 384, True), (256, 48, "CF16", 300, False), (256, 48, "C64", 280, True)])
+def test_blocked_lines(tmp_path_factory, C, T, dtype, blocks, one):
+    rows = 16384 // C * (2 if C >= 1024 else 1)
+    got = host_run(tmp_path_factory, f"""
+p = plan({C}, {T}, {blocks * rows}, 1, {dtype})
+events()
+assert L.pfb_execute(p, A, A, None, A, None) == 0
+result = [e[0] for e in events()]
+""")
+    assert (len(got) == 1 and "block_kernel" in got[0]) == one
