@@ -492,14 +492,29 @@ static pfb_status plan_single(const pfb_desc *d, pfb_plan *p)
                 : p->tp == 32                                        ? (ints && d->channels % 64 == 0 ? 32 : 128)
                 : (d->dtype == PFB_CI8 && p->tp == 16 && !wide_one) ? 64
                                                                      : 32;
-    // Launches of fewer waves than fit at once (eight a CU): shorter tiles
+    // Launches of few waves: shorter tiles, 16 rows up to 16 taps and 32 at 32
     // (1024 channels, 16 taps, 1000 spectra 9.3 -> 7.0 us; 32 taps, 2000
-    // spectra 51 -> 14). With an entry carried over from another length plans
-    // of up to 16 taps keep the heights above (900 spectra, one channel per
-    // lane 7.0 us, with 16 rows 5.9).
-    const double waves_per_row = (double)d->batch * (double)ceil_div(d->channels, 64 * p->fir_cpt);
+    // spectra 51 -> 14), in waves per CU with the heights above. Up to 16 taps
+    // below two, where every shape of 4 sizes, 4 windows and 4 types gains
+    // (1.0 to 1.8 times); at 600 to 1400 waves of 256 CUs int16 and float16
+    // still gain 0.96 to 1.3 below 4096 channels, complex64 and int8 0.8 to 1.2
+    // (2048 channels, 16 taps, int8, 4000 spectra 16.5, short 21.8). At 32 taps
+    // fewer taps than the window's make the first and the last tile test their
+    // rows, one after the other: complex64 below 5.5 (1400 waves 1.0 to 1.28),
+    // float16 below eight (1.6); with 32 taps themselves complex64 below two
+    // (800 waves 0.81 to 1.05), float16 below 2.75 (600 waves 1.04 to 1.9, 800
+    // 0.91 to 1.3); ragged channels, where every row is tested, below eight.
+    // With an entry carried over from another length plans of up to 16 taps
+    // keep the heights above (900 spectra, one channel per lane 7.0 us, with 16
+    // rows 5.9).
+    const double waves = (double)d->batch * (double)ceil_div(d->channels, 64 * p->fir_cpt) * (double)ceil_div(d->spectra, p->fir_sb);
+    const bool c64 = d->dtype == PFB_C64;
+    const double few = p->tp <= 16 ? (!c64 && d->dtype != PFB_CI8 && d->channels < 4096 ? 5.0 : 2.0)
+                       : d->channels % 64 != 0 ? 8.0
+                       : d->taps < 32          ? (c64 ? 5.5 : 8.0)
+                                               : (c64 ? 2.0 : 2.75);
     const bool shorten = p->tp == 32 || (p->tp <= 16 && !(tuned && te.carried));
-    if (shorten && waves_per_row * (double)ceil_div(d->spectra, p->fir_sb) < 8.0 * p->num_cus)
+    if (shorten && waves < few * p->num_cus)
         p->fir_sb = p->tp <= 16 ? 16 : 32;
     p->fir_segments = tuned && te.segments >= 0 ? te.segments != 0 && fir_segments_supported(*d)
                                                 : fir_segments_pay(*d, p->num_cus);

@@ -185,3 +185,17 @@ assert L.pfb_execute(p, A, A, None, A, None) == 0
 result = [e[0] for e in events()]
 """)
     assert (len(got) == 1 and "block_kernel" in got[0]) == one
+
+
+@pytest.mark.parametrize("C,T,S,dtype,rows", [
+    # tall and short tiles as measured, us
+    (2048, 16, 4000, "CI8", 64),     # 16.5, 21.8
+    (1024, 32, 8000, "C64", 128),    # 25.4, 32.4
+    (1024, 16, 7600, "C64", 32),     # 24.2, 28.7
+    (4096, 8, 1000, "CF16", 32),     # 8.1, 8.8
+    (1024, 16, 900, "C64", 16),      # 9.0, 6.7
+    (1024, 32, 2000, "C64", 32),     # 28, 11
+    (1024, 20, 8000, "C64", 32), (1024, 20, 16000, "CF16", 32),
+    (1024, 16, 1600, "CI16", 16), (2048, 32, 2000, "CI8", 32)])
+def test_short_fir_tiles_for_few_waves(tmp_path_factory, C, T, S, dtype, rows):
+    assert host_run(tmp_path_factory, f"result = info(plan({C}, {T}, {S}, 1, {dtype}, FIR_ONLY)).fir_rows") == rows
