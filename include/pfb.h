@@ -211,8 +211,10 @@ pfb_status pfb_stream_reset(pfb_plan *plan, void *stream);
  *   taps      device, [T][channels] float32 (replicated by the library)
  *   Y         device, [spectra][subbands][channels][2] complex float32:
  *             bin k of polarisation p of sub-band b at Y[s][b][k][p].
- * The plan owns a filtered-spectra workspace (spectra*2*channels*subbands
- * complex values) and the replicated taps. pfb_execute/pfb_backward reject
+ * A plan whose call runs the FIR and the transform as launches of their own
+ * holds a filtered-spectra workspace (spectra*2*channels*subbands complex
+ * values) and the replicated taps, one whose call is a single launch neither
+ * (workspace_bytes of pfb_plan_get_info is 0). pfb_execute/pfb_backward reject
  * these plans (PFB_E_STATE).
  */
 pfb_status pfb_plan_create_vegas(int32_t channels, int32_t subbands, int32_t taps, int64_t spectra,

@@ -343,7 +343,12 @@ static int fused_tile_rows(int64_t B, int64_t S, int T, int log2c, int cus, bool
 // gx rows per fused adjoint tile: every tile transforms T - 1 halo rows
 // again and writes a tap-gradient partial. Two workgroups a CU pay at 256
 // channels only (65536 rows, 16 taps: 128-row tiles 92 us, 272-row ones 114;
-// 512 channels, 32768 rows: 64-row tiles 111, 144-row ones 102).
+// 512 channels, 32768 rows: 64-row tiles 111, 144-row ones 102). The partials
+// of short tiles cost the plan's creation memory, and from 2 MB on, where the
+// runtime maps new memory for each request, some 50 us: 256 channels, 4096
+// spectra, 8 taps 2.1 MB and 73 us, with 128-row tiles 0.27 MB and 20; that
+// plan's first adjoint call takes 15 us instead of 37 (1024 channels, 1024
+// spectra, 16 taps 100 us for 37, and 33 a call instead of 118).
 static int adjoint_tile_rows(int64_t B, int64_t rows, int T, int C, int cus)
 {
     return tile_rows(B, rows, 16, T + 10, T / 2 + 2, C <= 256 ? 2 * cus : cus);

@@ -38,6 +38,11 @@
 // 0.48, complex64 0.68 with H = 2). Blocks dealt to the XCDs one by one
 // instead of in runs: 2048 channels complex64 0.78 against 0.52 (H = 1).
 //
+// Registers: 256, the most that two waves per SIMD leave. The 16-tap windows
+// of four columns spill beyond them: int16 13, 13 and 15 and float16 15, 9
+// and 13 registers at 2048, 4096 and 8192 channels, int8 7 at 8192 (32 to 64
+// bytes of scratch a lane); no other instance does.
+//
 // Sums take their taps in ascending order from one accumulator, with the taps
 // zero-padded at the front to TP, and the transform's radices, twiddles and
 // order of operations are the split path's: both give the same bits (at 33 to

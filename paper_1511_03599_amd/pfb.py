@@ -312,7 +312,8 @@ class Plan:
 
 class BatchedPlan:
     """Many independent single-stream beams (complex64), each with its own
-    (C, T, S), run by one persistent kernel launch per call."""
+    (C, T, S): the small ones by one persistent kernel launch per call, beams
+    that fill the GPU by launches of their own on the same stream."""
 
     def __init__(self, beams):
         """beams: list of (C, T, S) tuples."""

@@ -1,6 +1,7 @@
-"""Tiles and transform schedules of every shape the size rules give. Fused tiles of every height the tile rule gives: from one transform round
-(8 or 16 rows) at short streams to several hundred rows, with streams that end
-inside, at and just past a tile."""
+"""Tiles and transform schedules of every shape that the size rules give. Fused
+tiles: from one transform round (8 or 16 rows) at short streams to 128 rows,
+with streams that end inside, at and just past a tile; split adjoint tiles;
+mixed-radix schedules and groups."""
 import numpy as np
 import pytest
 
