@@ -354,21 +354,33 @@ static int adjoint_tile_rows(int64_t B, int64_t rows, int T, int C, int cus)
     return tile_rows(B, rows, 16, T + 10, T / 2 + 2, C <= 256 ? 2 * cus : cus);
 }
 
+// Least rows per tile of the tap gradient: a quarter of the partials is added
+// one after the other, so a tile shorter than rows / 1024 makes those sums
+// longer than the 256 rows that the tallest tile adds, and less exact (64
+// channels, 8 taps, 100000 spectra: relative error of the tap gradient 5.3e-7
+// with 16-row tiles, 4.6e-7 with 256 rows, 4.1e-7 with 96).
+static int least_gradient_rows(int64_t rows, int u)
+{
+    return (int)ceil_div(std::min<int64_t>(256, ceil_div(rows, 1024)), u) * u;
+}
+
 // Raw spectra per wave tile of the split adjoint (one wave per 64 channels),
 // whole blocks of its unrolled loop: enough waves for twice the eight that
 // the registers allow per CU, and no more than 160 rows (128 at 32 taps, 256
 // at 64), where the history that a tile reads again is small and the waves in
-// flight still sweep a narrow band of rows. The whole adjoint at 256-row
+// flight still sweep a narrow band of rows, unless the partials ask for more
+// (narrow rows, whose many partials also take the reduction long: 64 channels,
+// 65536 spectra, 8 taps, 16 rows 78 us, 64 rows 44). The whole adjoint at 256-row
 // tiles, as every size had, against these: 128 channels x 4000 spectra x 3
 // 141 -> 27 us, 2048 x 10000 x 3 606 -> 462, 4096 x 8192 x 2 610 -> 518.
 static int split_adjoint_rows(const pfb_desc &d, int tp, int cus)
 {
     const int u = tp > 16 ? tp : 16, most = tp <= 16 ? 160 : tp == 32 ? 128 : 256;
+    const int64_t raw = d.spectra + d.taps - 1;
     const double waves = (double)d.batch * (double)ceil_div(d.channels, 64);
-    const double rows = waves * (double)(d.spectra + d.taps - 1) / (16.0 * cus);
-    if (rows >= most)
-        return most;
-    return (int)std::max<int64_t>(1, ceil_div((int64_t)rows, u)) * u;
+    const double rows = waves * (double)raw / (16.0 * cus);
+    const int sb = rows >= most ? most : (int)std::max<int64_t>(1, ceil_div((int64_t)rows, u)) * u;
+    return std::max(sb, least_gradient_rows(raw * d.batch, u));
 }
 
 // Filtered spectra per wave tile of the tap gradient alone (gh_partial_kernel).
@@ -390,14 +402,15 @@ static int tap_gradient_rows(const pfb_desc &d, int tp, int cus)
     const int u = tp > 16 ? tp : 16;
     const double B = (double)d.batch, S = (double)d.spectra;
     const double bytes_us = 16.0 * B * S * (double)d.channels / (4.5e6 * cus / 256.0);
-    int best = u;
+    const int least = least_gradient_rows(d.spectra * d.batch, u);
+    int best = least;
     double best_us = 0.0;
-    for (int sb = u; sb <= 256; sb += u) {
+    for (int sb = least; sb <= 256; sb += u) {
         const int64_t tiles = ceil_div(d.spectra, sb);
         const int64_t clean = std::min(tiles, std::max<int64_t>(0, d.spectra + d.taps - tp) / sb);
         const int64_t tested = clean == tiles ? 0 : clean < tiles - 1 ? sb : d.spectra - (tiles - 1) * sb;
         const double us = bytes_us * (1.0 + 0.75 * (tp - 1) / sb) + 0.25 * (double)tested + 0.011 * B * (double)tiles + 0.04 * sb;
-        if (sb == u || us < best_us) {
+        if (sb == least || us < best_us) {
             best_us = us;
             best = sb;
         }

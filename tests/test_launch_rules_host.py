@@ -199,3 +199,23 @@ result = [e[0] for e in events()]
     (1024, 16, 1600, "CI16", 16), (2048, 32, 2000, "CI8", 32)])
 def test_short_fir_tiles_for_few_waves(tmp_path_factory, C, T, S, dtype, rows):
     assert host_run(tmp_path_factory, f"result = info(plan({C}, {T}, {S}, 1, {dtype}, FIR_ONLY)).fir_rows") == rows
+
+
+@pytest.mark.parametrize("C,T,S,B", [(64, 8, 100000, 1), (128, 16, 65536, 1), (32, 4, 1000, 300), (128, 24, 70000, 2),
+                                     (64, 50, 90000, 1), (4096, 16, 8192, 2), (96, 16, 300000, 1)])
+def test_tap_gradient_sums_are_no_longer_than_before(tmp_path_factory, C, T, S, B):
+    """The longest serial sum, of a tile's rows or of a quarter of the
+    partials, is no longer than 256-row tiles make it."""
+    rows, (both, alone) = host_run(tmp_path_factory, f"""
+p = plan({C}, {T}, {S}, {B})
+def tiles(gx, kernel):
+    events()
+    assert L.pfb_backward(p, A, A, A, gx, A, None) == 0
+    return sum(n for k, n in events() if kernel in k) * 4 // {-(-C // 64)}
+result = [info(p).backward_rows, [tiles(A, "gxgh" if {T} <= 32 else "gh_partial"), tiles(None, "gh_partial")]]
+""")
+    raw = S + T - 1
+    most = max(256, B * -(-raw // 256) // 4)
+    assert max(both, alone) // 4 <= most * 1.05 + 2
+    if T <= 32:
+        assert rows <= 256 and B * -(-raw // rows) // 4 <= most
